@@ -682,6 +682,7 @@ int cvx_read_records(cvx_ctx* ctx, int canvas_id, uint64_t first, uint64_t count
   CVX_HIP(hipSetDevice(ctx->device));
   CVX_HIP(hipStreamSynchronize(ctx->stream));
   CVX_HIP(hipMemcpy(out, (const uint8_t*)c.rec + first * 16, count * 16, hipMemcpyDeviceToHost));
+  for (uint64_t i = 0; i < count; ++i) out[4 * i] = cvx::public_x(out[4 * i]);
   return CVX_OK;
 }
 

@@ -81,6 +81,14 @@ __device__ __forceinline__ uint32_t twice_plus(uint32_t c, uint64_t b) {
   return r;
 }
 
+// c + b for a per-lane bit given as a lane mask, the same way.
+__device__ __forceinline__ uint32_t plus(uint32_t c, uint64_t b) {
+  uint32_t r;
+  uint64_t co;
+  asm("v_addc_co_u32_e64 %0, %1, 0, %2, %3" : "=v"(r), "=s"(co) : "v"(c), "s"(b));
+  return r;
+}
+
 // Cell indices between true and direction-normalised form (an involution):
 // component k xor all ones when the ray travels down axis k.
 __device__ __forceinline__ V3<uint32_t> flip(V3<uint32_t> c, const V3<bool>& up) {
@@ -231,7 +239,7 @@ template <class Real>
 __device__ __forceinline__ bool descend(const void* rec, uint32_t n_nodes, const V3<Real>& q,
                                         const V3<bool>& up, uint32_t& I, uint32_t& dep,
                                         V3<uint32_t>& c, uint4& r) {
-  while (!(r.x & 1u)) {
+  while (!is_leaf(r.x)) {
     if (r.x >= n_nodes - 7u) return false;
     const Real h = (Real)ldexp(1.0, -(int)dep);
     uint32_t oct = 0;
@@ -279,14 +287,14 @@ __device__ __forceinline__ V3<uint32_t> deep_coords(const V3<double>& q, const V
 __device__ __forceinline__ bool descend_int(const void* rec, uint32_t n_nodes, V3<uint32_t> C,
                                             uint32_t D, uint32_t& I, uint32_t& dep,
                                             V3<uint32_t>& c, uint4& r) {
-  if (r.x & 1u) return true;
+  if (is_leaf(r.x)) return true;
   for (int k = 0; k < 3; ++k) {
     const uint32_t lo = get(c, k) << (D - dep);
     const uint32_t hi = lo + ((1u << (D - dep)) - 1u);
     const uint32_t ck = get(C, k);
     set(C, k, ck < lo ? lo : (ck > hi ? hi : ck));
   }
-  while (!(r.x & 1u)) {
+  while (!is_leaf(r.x)) {
     if (r.x >= n_nodes - 7u) return false;
     const uint32_t sh = D - dep - 1u;
     uint32_t oct = 0;
@@ -312,7 +320,7 @@ __device__ __forceinline__ void locate_top(const DView& v, const V3<uint32_t>& C
     const uint32_t x = C.x >> (D - L), y = C.y >> (D - L), z = C.z >> (D - L);
     I = v.top[x + side * (y + side * z)];
     r = ld_rec(v.rec, I);
-    dep = (r.x & 1u) ? ((r.x >> 1) & 63u) : L;
+    dep = is_leaf(r.x) ? leaf_depth(r.x) : L;
   } else {
     I = (C.x >> D) + v.R * ((C.y >> D) + v.R * (C.z >> D));
     r = ld_rec(v.rec, I);
@@ -405,32 +413,54 @@ __device__ __forceinline__ float kappa_of(uint2 p) {
 // ----------------------------------------------------------------------------
 // FP32_REBASED: cell-local FP32 traversal (Sec. 6.1-6.2) as a certified DDA.
 //
-// After a rebase at the entry point p0 (ray parameter te) of a cell, lengths
-// are measured in "base units", the edge of a cell of depth db (a few levels
-// below the current leaf), from p0: s = (t - te) / h_db.  For every axis k the
-// face plane of the current leaf that lies ahead of the ray (its far plane in
-// the travel direction) is held as an exact integer offset N_k, in base cells,
-// from the far plane of the rebase cell, whose s-value S0_k was computed in
-// FP64.  The far plane's s-value is S_k = S0_k + N_k / |d_k| with a constant
-// error bound (no drift with the number of steps, unlike the per-step update
-// analysed in Sec. 6.3):
-//   |S_k - exact| <= ALPHA (S0_k + |N_k| / |d_k|) + beta,  beta = 2^(db-50) tR,
-// ALPHA covering the FP32 roundings of S0, 1/|d|, N and the fused update.
-// Exit = argmin S_k, certified when the lower bounds of the other two exceed
-// its upper bound; otherwise the FP64 face planes decide.  A same-depth
-// step adds the cell width w = 2^(db-dep) to N on the exit axis; a step into a
-// coarser leaf adds the integer distance to its far planes; a refined cell is
-// descended one level per iteration by comparing the entry s with the
-// mid-plane s-values (certified likewise).  FP64 rebuilds the state
-// ("rebase") only at the ray's start, after an FP64 decision, or when a
-// descent goes below db or cannot be certified.
+// Lengths are measured in base cells, the edge 2^-D of a cell at the pool's
+// deepest level D, from the entry point p0 of the last rebase (ray parameter
+// te): s = (t - te) 2^D.  A cell is held by its width 2^lw base cells and, per
+// axis, by E_k, the index of its last base cell along the ray in direction-
+// normalised form (index xor all ones when the ray travels down the axis), so
+// the low lw bits of every E_k are ones and
+//   next cell across face k        E_k + 1, low bits filled again (one add
+//                                  with the axis lane mask as carry, one or),
+//   coarser leaf                   the same with the coarser leaf's low bits,
+//   near child of a refined cell   E_k with bit lw - 1 cleared,
+//   sibling across face k          when bit lw of E_k is 0.
+// The far plane of the cell (the one ahead of the ray) has the s-value
+//   S_k = S0_k + (E_k - E0_k) / |d_k|,
+// E0_k the base cell that holds p0 and S0_k its far plane's s-value, computed
+// in FP64 and rounded once.  E_k >= E0_k for every cell the ray visits after
+// p0, so both terms are >= 0 and, u = 2^-24 (the FP32 roundings of N = E - E0,
+// of 1/|d|, of S0 and of the fused update),
+//   |S_k - exact| <= 3 u S_k + beta,   beta = 2^(D-50) tR (the FP64 rebase),
+// with no drift in the number of steps (unlike the per-step update analysed in
+// Sec. 6.3).  Exit = argmin S_k, certified when the two other planes exceed
+// Smin (1 + 12 u) + 2.25 beta, one threshold for all three axes; otherwise the
+// FP64 face planes decide.  A refined cell is descended by comparing the entry
+// s with the mid-plane s-values, certified with |N| in place of N.  FP64
+// rebuilds the frame ("rebase") at the ray's start, after an FP64 decision,
+// where a descent cannot be certified and where the frame has become too
+// coarse for the leaf (GUARD).
+//
+// Bound by vector instruction issue (and, in small launches, by the latency
+// of one iteration: the neighbour's record, from beyond the L2).  A leaf step
+// is 65 vector instructions, a descent 44 in the same iteration.  A frame of
+// far planes at depth + 8 with a bound per axis, separate cell indices and
+// plane offsets, and an iteration of its own per descent, took 94 and 45 and
+// measured (one MI355X, whole call, before / after) 1214 / 959 us on a
+// 1920x1080 stereo pair of a 33 M-node depth-24 canvas, 813 / 661 us on a
+// 1024x1024 view of depth-29 leaves and 605 / 534 us on a 2160x2160 stereo
+// pair whose rays stop at an opacity.
 // ----------------------------------------------------------------------------
-constexpr float ALPHA = 0x1p-21f;
-// certification bound per plane value: 1.0625 (ALPHA G + beta) plus 2^-23 G
-// for the FP32 rounding of the comparison (G >= |value|), folded into one fma
-constexpr float ALPHA_C = 0x1p-21f * 1.0625f + 0x1p-23f;
-constexpr float BETA_C = 1.0625f;
-constexpr uint32_t DB_MARGIN = 8;
+constexpr float CERT_K = 1.0f + 0x1p-21f + 0x1p-22f;  // 1 + 12 u
+constexpr float CERT_B = 2.25f;
+// descents: 3 u for each value and u for the rounding of their difference
+constexpr float DESC_A = 0x1p-22f;
+// a frame serves a leaf while 16 u s + 2 beta, more than the error of a
+// segment's length, stays within 2^-10 of the leaf's edge
+constexpr float GUARD_A = 0x1p-20f;
+constexpr float GUARD_MAX = 0x1p-10f;
+// s grows by at most sqrt(3) leaf edges per step through leaves of one size,
+// so the guard is tested every GUARD_EVERY steps (and at every descent)
+constexpr uint32_t GUARD_EVERY = 16;
 
 // Per-lane LDS slot holding the FP64 eye, direction and reciprocal direction
 // of the lane's ray, [9][blockDim.x] doubles (component-major, so lanes read
@@ -471,7 +501,8 @@ struct RefillJob {
 // FP32_REBASED traversal of one lane: one ray (REFILL = false: o, d, inv,
 // en, up describe it) or, REFILL = true, the rays a RefillJob hands out one
 // after another, each written to its pixel when it ends.  The per-ray
-// arithmetic is the same in both, so both give the same pixels.
+// arithmetic is the same in both, so both give the same pixels (up to the
+// guard, which a refilled lane tests at every step).
 // SPLIT = true: the ray's chord is cut at ray parameter t_end (the end of a
 // chord piece; infinity for the last piece): the leaf holding t_end
 // contributes only the part before it, decided like an exit (certified, else
@@ -487,74 +518,89 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
   static_assert(!(REFILL && SPLIT), "chord pieces are traced one per lane");
   const void* rec = v.rec;
   const void* payp = v.pay;
-  const bool use_stop = v.alpha_stop < 1.0f;
+  const uint32_t D = v.max_depth;
+  // T <= t_stop never holds without an opacity stop
+  const float t_stop = v.alpha_stop < 1.0f ? v.t_stop : -1.0f;
   V3<float> tD;
   bool anypar = false;
   float tR = 0.0f;
   V3<bool> up;
+  // the travel directions as lane masks, in scalar registers (REFILL: the
+  // lanes' rays begin at different times, so the masks are made from `up`)
+  uint64_t upm[3] = {0, 0, 0};
+  auto up_mask = [&](int k) __attribute__((always_inline)) -> uint64_t {
+    return REFILL ? lanes(get(up, k)) : upm[k];
+  };
+  uint64_t parm = 0;  // lanes whose ray is parallel to an axis, the same way
+  auto par_mask = [&]() __attribute__((always_inline)) -> uint64_t {
+    return REFILL ? lanes(anypar) : parm;
+  };
   V3<double> q;
-  uint32_t I = 0, dep = 0;
-  // cell indices at depth dep, direction-normalised: c_k xor all ones when
-  // the ray travels down axis k, so that the next cell along the ray is
-  // always c_k + 1 and an arithmetic shift right gives the parent's index
-  // (R 2^max_depth <= 2^30: the sign bit is the direction)
-  V3<uint32_t> c;
+  uint32_t I = 0;
+  uint32_t lw = 0;               // the cell is 2^lw base cells wide
+  V3<uint32_t> E{0, 0, 0};       // its last base cell per axis, normalised
+  V3<uint32_t> E0{0, 0, 0};      // the frame's reference base cell
   uint4 r;
   uint2 pay = make_uint2(0u, 0u);
-  uint32_t db = 0, w = 1;
   V3<float> S0{0.f, 0.f, 0.f};
-  V3<int32_t> Nk{0, 0, 0};
-  float s_ent = 0.0f, e_ent = 0.0f, betac = 0.0f;  // betac = BETA_C beta
-  bool bad = false;  // a node index outside the pool (never for a validated pool)
+  float s_ent = 0.0f, beta = 0.0f;
   double te_last = 0.0;  // trace mode: ray parameter of the last rebase
   float T = 1.0f;
   V3<float> C{0.f, 0.f, 0.f};
   uint32_t n_rec = 0;
   // bit (1, 2 or 4) of the axis of the face the current cell was entered
-  // through; 0 where the ray started inside the canvas
-  uint32_t kbe = 0;
-  uint32_t ub = 0;
+  // through (set by every move)
+  uint32_t kbe = 1u;
   uint32_t step = 0;
-  uint32_t end_Nn = 0, end_nc = 0, end_dep = 0;  // the move the ray ended on
-  // the ray ended at the canvas boundary or the opacity stop; it leaves the
-  // loop at the top of the next iteration (one exit, so the loop-carried
-  // values need no copies for a second one)
-  bool done = false;
   // SPLIT: s-value of the piece's end and its error bound (BIGF: no end)
   float s_end = BIGF, e_end = 0.0f;
-  // FP64 rebuild of the base frame at ray parameter te (q = FP64 point); the
+  // FP64 face plane of axis k ahead of the ray (back = 0) or, with back = the
+  // cell's width, behind it: +-(E + 1 - back) 2^-D, exact
+  auto plane = [&](int k, int32_t back) __attribute__((always_inline)) -> double {
+    const double n = (double)((int32_t)get(E, k) - back) + 1.0;
+    return ldexp(get(up, k) ? n : -n, -(int)D);
+  };
+  // FP64 rebuild of the frame at ray parameter te (q = FP64 point); the
   // current cell I is descended first when it is refined.
-  auto rebase = [&](double te) __attribute__((always_inline)) {
+  auto rebase = [&](double te, bool& stop) __attribute__((always_inline)) {
     if (TRACE) te_last = te;
+    uint32_t dep = D - lw;
     const uint32_t d0 = dep;
-    V3<uint32_t> cr = flip(c, up);  // true indices
-    bad = bad || !descend_int(rec, v.n_nodes, deep_coords(q, up, v.R, v.max_depth), v.max_depth,
-                              I, dep, cr, r);
+    V3<uint32_t> cr{(uint32_t)((int32_t)E.x >> lw), (uint32_t)((int32_t)E.y >> lw),
+                    (uint32_t)((int32_t)E.z >> lw)};
+    cr = flip(cr, up);  // true indices
+    V3<uint32_t> Cd = deep_coords(q, up, v.R, D);
+    if (!descend_int(rec, v.n_nodes, Cd, D, I, dep, cr, r)) {
+      // a node index outside the pool, which no validated pool has
+      out.flags |= CVX_RAYFLAG_BAD_LINK;
+      stop = true;
+    }
     if (STATS) acc.descent += dep - d0;
     pay = ld_pay_t<SMALL>(payp, I);
-    db = dep + DB_MARGIN < v.max_depth ? dep + DB_MARGIN : (v.max_depth > dep ? v.max_depth : dep);
-    w = 1u << (db - dep);
-    const double hd = ldexp(1.0, -(int)dep);
+    lw = D - dep;
+    const uint32_t low = (1u << lw) - 1u;
     // rolled: one FP64 plane live at a time; the plane's parameter uses the
     // ray's reciprocal direction (a few FP64 ulp, inside the rebase term of
     // the bound)
 #pragma unroll 1
     for (int k = 0; k < 3; ++k) {
-      const double X = (double)get(cr, k) * hd + (get(up, k) ? hd : 0.0);  // exact
+      // the base cell of p0, inside the leaf
+      const uint32_t lo = get(cr, k) << lw, ck = get(Cd, k);
+      const uint32_t b = ck < lo ? lo : (ck > lo + low ? lo + low : ck);
+      const uint32_t fm = get(up, k) ? 0u : ~0u;
+      const double X = ldexp((double)(b + (get(up, k) ? 1u : 0u)), -(int)D);  // exact
       const double Tk = (X - slot.at(k)) * slot.at(6 + k);
-      set(S0, k, get(tD, k) == 0.0f ? BIGF : (float)ldexp(Tk - te, (int)db));
+      set(S0, k, get(tD, k) == 0.0f ? BIGF : (float)ldexp(Tk - te, (int)D));
+      set(E0, k, b ^ fm);
+      set(E, k, (lo ^ fm) | low);
     }
-    c = flip(cr, up);
-    Nk = V3<int32_t>{0, 0, 0};
     s_ent = 0.0f;
-    const float beta = ldexpf(tR, (int)db - 50);
-    e_ent = beta;
-    betac = beta * BETA_C;
+    beta = ldexpf(tR, (int)D - 50);
     if constexpr (SPLIT) {
-      // (t_end - te) 2^db rounded to FP32 (2^-24 relative) after an FP64
+      // (t_end - te) 2^D rounded to FP32 (2^-24 relative) after an FP64
       // difference within beta
       const bool has_end = t_end < __builtin_inf();
-      s_end = has_end ? (float)ldexp(t_end - te, (int)db) : BIGF;
+      s_end = has_end ? (float)ldexp(t_end - te, (int)D) : BIGF;
       e_end = has_end ? beta + __builtin_fabsf(s_end) * 0x1p-23f : 0.0f;
     }
     if (STATS) acc.rebase++;
@@ -562,15 +608,17 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
   // ray start: the FP64 entry point, the first leaf and the first frame (Rd =
   // the canvas side R in FP64)
   auto begin = [&](const V3<double>& o, const V3<double>& d, const V3<double>& inv,
-                   const Entry& en, const V3<bool>& up_, double Rd) __attribute__((always_inline)) {
+                   const Entry& en, const V3<bool>& up_, double Rd)
+      __attribute__((always_inline)) -> bool {
     slot.put(o, d, inv);
-    for (int k = 0; k < 3; ++k) {
-      const double dk = get(d, k);
-      set(tD, k, __builtin_fabs(dk) >= 0x1p-60 ? 1.0f / __builtin_fabsf((float)dk) : 0.0f);
-    }
+    for (int k = 0; k < 3; ++k)
+      set(tD, k, __builtin_fabs(get(d, k)) >= 0x1p-60 ? (float)__builtin_fabs(get(inv, k)) : 0.0f);
     anypar = tD.x == 0.0f || tD.y == 0.0f || tD.z == 0.0f;
     tR = (float)(en.t1 + Rd + 1.0);
     up = up_;
+    if constexpr (!REFILL)
+      for (int k = 0; k < 3; ++k) upm[k] = lanes(get(up_, k));
+    if constexpr (!REFILL) parm = lanes(anypar);
     // first leaf: the view's shared eye leaf, else FP64 point location from
     // the top-level table or the root array (descended to the leaf by the
     // rebase)
@@ -579,35 +627,27 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
       if (k == en.kin) qk = en.side ? Rd : 0.0;
       set(q, k, qk < 0.0 ? 0.0 : (qk > Rd ? Rd : qk));
     }
-    dep = 0;
+    uint32_t dep = 0;
+    V3<uint32_t> c;
     start_leaf(v, q, up, I, dep, c, r, shared_start);
     c = flip(c, up);
     if (STATS) acc.descent += dep;
+    lw = D - dep;
+    E = V3<uint32_t>{c.x << lw, c.y << lw, c.z << lw};
     pay = make_uint2(0u, 0u);
-    db = 0;
-    w = 1;
-    bad = false;
     te_last = 0.0;
-    rebase(en.t0);
+    bool lost = false;
+    rebase(en.t0, lost);
     T = 1.0f;
     C = V3<float>{0.f, 0.f, 0.f};
     n_rec = 0;
-    kbe = en.kin < 0 ? 0u : 1u << en.kin;
-    // travel direction bits (x | y<<1 | z<<2) in one opaque register: the
-    // exit-axis bit is one bit-field extract, not a chain of selects
-    ub = opaque((up.x ? 1u : 0u) | (up.y ? 2u : 0u) | (up.z ? 4u : 0u));
+    kbe = 1u;
     step = 0;
-    end_Nn = end_nc = end_dep = 0;
-    done = false;
+    return !lost;
   };
   // flags, colour and counts of the ray that ended
   auto finish = [&]() __attribute__((always_inline)) {
-    if (bad)
-      out.flags |= CVX_RAYFLAG_BAD_LINK;
-    else if (!done && step >= v.max_steps)
-      out.flags |= CVX_RAYFLAG_STEP_CAP;
-    else if (end_Nn >= v.n_nodes && end_nc < (v.R << end_dep))
-      out.flags |= CVX_RAYFLAG_BAD_LINK;  // a null link inside the canvas
+    if (step >= v.max_steps) out.flags |= CVX_RAYFLAG_STEP_CAP;
     const float k255 = 1.0f / 255.0f;
     out.rgba[0] = C.x * k255;
     out.rgba[1] = C.y * k255;
@@ -615,7 +655,7 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
     out.rgba[3] = 1.0f - T;
     out.T = T;
     out.n = n_rec;
-    out.steps = done ? step : step + 1;  // a ray that ended left one iteration later
+    out.steps = step + 1;
     if (STATS) acc.leaves += n_rec;
   };
   // REFILL: the pixel of the lane's current ray; starting ray i of the job
@@ -649,7 +689,10 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
       write_pixel();
       return false;
     }
-    begin(o, d, inv, en, V3<bool>{d.x > 0.0, d.y > 0.0, d.z > 0.0}, Rd);
+    if (!begin(o, d, inv, en, V3<bool>{d.x > 0.0, d.y > 0.0, d.z > 0.0}, Rd)) {
+      write_pixel();
+      return false;
+    }
     return true;
   };
   bool alive = true;
@@ -659,7 +702,7 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
     alive = begin_job_ray(threadIdx.x & 63u);
     wait_for = job->refill_min;
   } else {
-    begin(o_in, d_in, inv_in, en_in, up_in, (double)v.R);
+    if (!begin(o_in, d_in, inv_in, en_in, up_in, (double)v.R)) return;
   }
   // REFILL: rounds of traversal; a round ends when wait_for lanes wait, then
   // the waiting lanes take the job's next rays (ranked by a ballot), and once
@@ -672,67 +715,21 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
       if ((uint32_t)__popcll(__ballot(!alive)) >= wait_for) break;
       if (!alive) continue;
     }
-    if (step >= v.max_steps || bad || done) {
+    if (step >= v.max_steps) {
       if constexpr (!REFILL) break;
       finish();
       write_pixel();
       alive = false;
       continue;
     }
-    // s-values of the far planes (leaf) or of the mid-planes (refined cell)
-    // and their error bounds; a refined cell's mid-plane lies half a cell
-    // before its far plane
-    const bool leaf = r.x & 1u;
-    const uint32_t half = w >> 1;
-    const int32_t off = (int32_t)(half & ~(uint32_t)(-(int32_t)(r.x & 1u)));  // 0 for a leaf
-    V3<float> S, eb;
-    for (int k = 0; k < 3; ++k) {
-      const float Nf = (float)(get(Nk, k) - off);
-      set(S, k, __builtin_fmaf(Nf, get(tD, k), get(S0, k)));
-      set(eb, k, __builtin_fmaf(ALPHA_C, __builtin_fmaf(__builtin_fabsf(Nf), get(tD, k), get(S0, k)),
-                                betac));
-    }
-    bool need64 = false;
-    if (!leaf) {
-      // ---- refined cell entered through its near face on axis kbe: one level.
-      // A refined cell is only reached by a leaf step (kbe != 0), and its
-      // neighbours are of the same depth, so on axis kbe the entry value s_ent
-      // and the mid-plane differ by exactly half a cell in N (>= 1 base cell,
-      // far above the bounds): the entry side of that axis needs no test.
-      need64 = w < 2u || anypar;
-      if (r.x >= v.n_nodes - 7u) {  // ends the ray at the top of the loop
-        bad = true;
-        continue;
-      }
-      uint32_t oct = 0;
-      for (int k = 0; k < 3; ++k) {
-        const float diff = s_ent - get(S, k);
-        const bool far = diff >= 0.0f;
-        const bool sure = __builtin_fabsf(diff) > e_ent + get(eb, k);
-        need64 = need64 || !sure;
-        const uint32_t b = (get(up, k) == far) ? 1u : 0u;  // the child's octant bit
-        oct |= b << k;
-        set(Nk, k, get(Nk, k) - (far ? 0 : (int32_t)half));
-        set(c, k, twice_plus(get(c, k), lanes(far)));  // normalised: the far child is next
-      }
-      if (!need64) {
-        I = r.x + oct;
-        ++dep;
-        w = half;
-        r = ld_rec_t<SMALL>(rec, I);
-        pay = ld_pay_t<SMALL>(payp, I);
-        if (STATS) acc.descent++;
-        continue;
-      }
-      // undo the speculative update; the FP64 rebase descends from here
-      for (int k = 0; k < 3; ++k) {
-        const uint32_t ck = get(c, k);
-        const bool far = (ck & 1u) != 0u;
-        set(Nk, k, get(Nk, k) + (far ? 0 : (int32_t)half));
-        set(c, k, (uint32_t)((int32_t)ck >> 1));
-      }
-    } else {
-      // ---- leaf: exit face, certified against the error bounds
+    // stop: the ray ends (canvas boundary, opacity stop); it leaves the loop at
+    // the bottom, the only exit, so the loop-carried values need no copies
+    bool need64 = false, stop = false;
+    if (is_leaf(r.x)) {
+      // ---- leaf: s-values of its far planes, exit face
+      V3<float> S;
+      for (int k = 0; k < 3; ++k)
+        set(S, k, __builtin_fmaf((float)(int32_t)(get(E, k) - get(E0, k)), get(tD, k), get(S0, k)));
       const float Smin = __builtin_fminf(S.x, __builtin_fminf(S.y, S.z));
       // exit axis (ties to the lower axis) as its bit kbit (1, 2, 4), also
       // held one-hot as lane masks mx, my (z when neither) for the selects
@@ -745,60 +742,49 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
       // Its record load is issued as soon as the exit axis is known (again
       // after an FP64 decision), so that its latency overlaps the
       // certification and the composite instead of stalling the move.
-      uint32_t nc = 0;  // normalised index of the next cell on the exit axis
-      bool upk = false, inner = false;
+      uint32_t Ex = 0;  // E on the exit axis
+      bool inner = false;
       auto neighbour = [&](uint4 rr) __attribute__((always_inline)) -> uint32_t {
-        const uint32_t ck = mx ? c.x : (my ? c.y : c.z);  // normalised
-        upk = (ub & kbit) != 0u;
-        nc = ck + 1u;
-        const bool root = dep == 0;
-        // the sibling lies across the face when the normalised index is even
-        // (the cell is even going up, odd going down); siblings differ in
-        // the exit axis's octant bit only
-        inner = !root && (ck & 1u) == 0u;
-        uint32_t sib = I ^ kbit;
-        if (root) {
-          // root array (rare): kept as a branch, not flattened into selects
-          asm volatile("");
-          const uint32_t ncr = upk ? nc : ~nc;  // true index; wraps to ~0 below 0
-          const uint32_t rs = mx ? 1u : (my ? v.R : v.R * v.R);
-          sib = ncr >= v.R ? CVX_NONE : (upk ? I + rs : I - rs);
-        }
+        Ex = mx ? E.x : (my ? E.y : E.z);
+        // the sibling lies across the face when the normalised index is even;
+        // siblings differ in the exit axis's octant bit only
+        inner = __builtin_amdgcn_ubfe(Ex, lw, 1u) == 0u;
         const uint32_t link = mx ? rr.y : (my ? rr.z : rr.w);
-        return (root || inner) ? sib : link;
+        uint32_t N = inner ? I ^ kbit : link;
+        if (lw == D) {
+          asm volatile("");  // root array (rare): a branch, not selects
+          inner = false;
+          const bool upk = mx ? up.x : (my ? up.y : up.z);
+          const uint32_t cn = (uint32_t)((int32_t)Ex >> lw) + 1u;
+          const uint32_t ncr = upk ? cn : ~cn;  // true index; wraps to ~0 below 0
+          const uint32_t rs = mx ? 1u : (my ? v.R : v.R * v.R);
+          N = ncr >= v.R ? CVX_NONE : (upk ? I + rs : I - rs);
+        }
+        return N;
       };
       // the canvas boundary has null links (CVX_NONE >= n_nodes) and so would
-      // a broken pool (the two are told apart after the loop); a null
-      // neighbour's load reads node 0 instead
+      // a broken pool; a null neighbour's load reads node 0 instead
       uint32_t Nn = neighbour(r);
       uint32_t In = Nn < v.n_nodes ? Nn : 0u;
       uint4 rn = ld_rec_t<SMALL>(rec, In);
-      const float emin = mx ? eb.x : (my ? eb.y : eb.z);
-      // certified when the lower bounds S_k - eb_k of the two other planes
-      // exceed the upper bound Smin + emin of the minimum: each of the two
-      // FP32 roundings is at most 2^-24 G of its plane, inside the 2^-23 G
-      // each bound carries for it.  The minimum's own test is always false
-      // (Smin - emin <= Smin + emin), so this is the majority of the three
-      // (lane masks: scalar logic, no vector count)
-      const float up_min = Smin + emin;
-      const uint64_t s0 = lanes(S.x - eb.x > up_min);
-      const uint64_t s1 = lanes(S.y - eb.y > up_min);
-      const uint64_t s2 = lanes(S.z - eb.z > up_min);
+      // certified when two planes exceed the threshold (the minimum's own test
+      // is always false, so this is the majority of the three)
+      const float thr = __builtin_fmaf(Smin, CERT_K, CERT_B * beta);
+      const uint64_t s0 = lanes(S.x > thr);
+      const uint64_t s1 = lanes(S.y > thr);
+      const uint64_t s2 = lanes(S.z > thr);
       const bool cert = lane((s0 & s1) | (s2 & (s0 | s1)));
-      // exit plane value and bound (the smallest one unless FP64 decides)
-      float Sx = Smin, ex = emin;
+      float Sx = Smin;  // exit plane value (the smallest one unless FP64 decides)
       if (!cert) {
         // FP64 decision from the exact face planes, t = (X - o_k) / d_k with
         // the ray's reciprocal direction (as the FP64 caster does; an ulp or
         // two changes a decision only inside the 1e-12 face band)
-        const double hd = ldexp(1.0, -(int)dep);
         double best = __builtin_inf();
         int kb = __builtin_ctz(kbit);
 #pragma unroll 1
         for (int k = 0; k < 3; ++k) {
-          const double X = (double)(get(c, k) ^ (get(up, k) ? 0u : ~0u)) * hd +
-                           (get(up, k) ? hd : 0.0);
-          const double tt = get(tD, k) == 0.0f ? __builtin_inf() : (X - slot.at(k)) * slot.at(6 + k);
+          const double tt =
+              get(tD, k) == 0.0f ? __builtin_inf() : (plane(k, 0) - slot.at(k)) * slot.at(6 + k);
           kb = tt < best ? k : kb;
           best = tt < best ? tt : best;
         }
@@ -806,7 +792,6 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
         mx = kb == 0;
         my = kb == 1;
         Sx = get(S, kb);
-        ex = get(eb, kb);
         Nn = neighbour(ld_rec_t<SMALL>(rec, I));
         In = Nn < v.n_nodes ? Nn : 0u;
         rn = ld_rec_t<SMALL>(rec, In);
@@ -815,7 +800,7 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
         if (STATS) acc.fp64_exit++;
       }
       if (TRACE) {
-        const double t = te_last + ldexp((double)Sx, -(int)db);
+        const double t = te_last + ldexp((double)Sx, -(int)D);
         for (int k = 0; k < 3; ++k) out.end[k] = slot.at(k) + t * slot.at(3 + k);
       }
       // SPLIT: does the piece end inside this leaf?  Certainly when the exit
@@ -826,41 +811,39 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
       bool cut = false;
       float Sl = Sx;  // where this leaf's segment ends
       if constexpr (SPLIT) {
-        const float eb_end = ex + e_end;
+        const float eb_end = __builtin_fmaf(DESC_A, Sx, beta) + e_end;
         if (Sx + eb_end >= s_end) {
           if (Sx - eb_end > s_end) {
             cut = true;
           } else {
-            const double hd = ldexp(1.0, -(int)dep);
             const int kx = __builtin_ctz(kbit);
-            const double X = (double)(get(c, kx) ^ (get(up, kx) ? 0u : ~0u)) * hd +
-                             (get(up, kx) ? hd : 0.0);
-            cut = (X - slot.at(kx)) * slot.at(6 + kx) > t_end;
+            cut = (plane(kx, 0) - slot.at(kx)) * slot.at(6 + kx) > t_end;
           }
         }
         Sl = cut ? s_end : Sx;
       }
-      // length precision guard: rebase once the bound on this segment's
-      // length exceeds 2^-10 of the leaf edge (w = 2^(db - dep) base cells),
-      // compared in leaf edges (a power-of-two scale: exact)
-      const float eseg = ex + e_ent;
-      need64 = need64 || ldexpf(eseg, (int)dep - (int)db) > 0x1p-10f;
-      float len = ldexpf(Sl - s_ent, (int)dep - (int)db);
-      len = len > 0.0f ? len : 0.0f;
+      const int nlw = (int)opaque(0u - lw);
+      // length precision guard (a uniform test but for refilled lanes)
+      if ((step & (GUARD_EVERY - 1u)) == GUARD_EVERY - 1u) {
+        asm volatile("");  // a branch, not selects
+        need64 = need64 || ldexpf(__builtin_fmaf(GUARD_A, Sx, 2.0f * beta), nlw) > GUARD_MAX;
+      }
       // composite; every visited leaf is recorded: for a ray outside the face
       // band the exact segment is positive even when it rounds to 0 here
-      // (kappa len as an FMA with a zero addend: the same rounding as the
-      // product, with the FP16 kappa taken as an operand, no conversion)
+      // (-log2(e) and the leaf's scale as one exact-scaled factor; kappa times
+      // it as an FMA with a zero addend: the same rounding as the product,
+      // with the FP16 kappa taken as an operand, no conversion)
       // (the absorbed share a = T - T e as one FMA, T updated in place)
-      const float e =
-          __builtin_amdgcn_exp2f(__builtin_fmaf(kappa_of(pay), len, 0.0f) * -1.4426950408889634f);
+      const float ds = __builtin_fmaxf(Sl - s_ent, 0.0f);
+      const float e = __builtin_amdgcn_exp2f(
+          __builtin_fmaf(kappa_of(pay), ds * ldexpf(-1.4426950408889634f, nlw), 0.0f));
       const float a = __builtin_fmaf(-T, e, T);
       T = T * e;
       C.x = __builtin_fmaf(a, (float)(pay.x & 0xffu), C.x);
       C.y = __builtin_fmaf(a, (float)((pay.x >> 8) & 0xffu), C.y);
       C.z = __builtin_fmaf(a, (float)((pay.x >> 16) & 0xffu), C.z);
-      if (TRACE) record(sk, n_rec, I, len);
-      ++n_rec;
+      if (TRACE) record(sk, n_rec, I, ldexpf(ds, nlw));
+      if (TRACE || STATS) ++n_rec;
       if constexpr (SPLIT) {
         if (cut) break;  // the piece ends inside this leaf (no move, no flags)
       }
@@ -868,19 +851,13 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
       // composite, so the record load has the whole step to arrive
       __builtin_amdgcn_sched_barrier(0);
       // ---- move to the neighbour (stop: bitwise, lane masks, not a branch)
-      const bool mz = !mx & !my;
-      const bool stop = (Nn >= v.n_nodes) | (use_stop & (T <= v.t_stop));
+      stop = (Nn >= v.n_nodes) | (T <= t_stop);
       if (stop) {
-        end_Nn = Nn;
-        end_nc = upk ? nc : ~nc;  // true index
-        end_dep = dep;
-        if constexpr (REFILL) {
-          finish();
-          write_pixel();
-          alive = false;
-          continue;
+        // a null link is the canvas boundary when the exit plane is
+        if (Nn >= v.n_nodes) {
+          const bool upk = mx ? up.x : (my ? up.y : up.z);
+          if (Ex + 1u != (upk ? v.R << D : 0u)) out.flags |= CVX_RAYFLAG_BAD_LINK;
         }
-        done = true;
       }
       // a ray that stopped still runs the move below (its results are not
       // used), on node 0 when its neighbour is null
@@ -888,37 +865,69 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
       I = In;
       r = rn;
       pay = ld_pay_t<SMALL>(payp, I);
-      const V3<uint32_t> co = c;
-      c.x = mx ? nc : c.x;
-      c.y = my ? nc : c.y;
-      c.z = mz ? nc : c.z;
       s_ent = Sx;
-      e_ent = ex;
       kbe = kbit;
-      // far planes move by one cell on the exit axis, and for a coarser
-      // leaf (m levels up) by the integer number of cells to its far planes:
-      // in normalised indices the coarse cell's far plane lies after fine
-      // cell (new | mask), so the plane advances by (new | mask) - old cells
-      const uint32_t dL = (r.x & 1u) ? ((r.x >> 1) & 63u) : dep;
-      const uint32_t m = dL < dep ? dep - dL : 0u;
-      const uint32_t mask = (1u << m) - 1u;
-      const uint32_t lw = db - dep;  // w = 2^lw
-      for (int k = 0; k < 3; ++k) {
-        const uint32_t cn = get(c, k);
-        set(Nk, k, get(Nk, k) + (int32_t)(((cn | mask) - get(co, k)) << lw));
-        set(c, k, (uint32_t)((int32_t)cn >> m));
-      }
-      w <<= m;
-      dep -= m;
+      // one base cell on along the exit axis, then the low bits of the new
+      // cell's width (a leaf's depth is in its record; a refined neighbour is
+      // as wide as the cell that was left)
+      lw = is_leaf(rn.x) ? (D | CVX_XLEAF) - rn.x : lw;
+      const uint32_t low = __builtin_amdgcn_ubfe(~0u, 0u, lw);
+      const uint64_t gx = lanes(kbit == 1u), gy = lanes(kbit == 2u);
+      E.x = plus(E.x, gx) | low;
+      E.y = plus(E.y, gy) | low;
+      E.z = plus(E.z, ~(gx | gy)) | low;
     }
-    if (need64 && !done) {
+    if (!is_leaf(r.x) && !need64 && !stop) {
+      // ---- refined cell: one level down, in the same iteration as the leaf
+      // step that entered it
+      const uint32_t half = 1u << (lw - 1u);
+      const float e_sum = __builtin_fmaf(DESC_A, s_ent, CERT_B * beta);
+      uint64_t far[3], sure = ~par_mask();
+      V3<uint32_t> Em;
+      for (int k = 0; k < 3; ++k) {
+        set(Em, k, get(E, k) - half);  // the last base cell before the mid-plane
+        const float Nf = (float)(int32_t)(get(Em, k) - get(E0, k));
+        const float diff = s_ent - __builtin_fmaf(Nf, get(tD, k), get(S0, k));
+        const float G = __builtin_fmaf(__builtin_fabsf(Nf), get(tD, k), get(S0, k));
+        far[k] = lanes(diff >= 0.0f);
+        sure &= lanes(__builtin_fabsf(diff) > __builtin_fmaf(DESC_A, G, e_sum));
+      }
+      // the frame must also be fine enough for the child
+      sure &= lanes(ldexpf(__builtin_fmaf(GUARD_A, s_ent, 2.0f * beta), 1 - (int)lw) <= GUARD_MAX);
+      need64 = !lane(sure);
+      if (!need64) {
+        // octant bits: the far child is the upper one where the ray goes up
+        const uint32_t oct = twice_plus(
+            twice_plus(lane(~(far[2] ^ up_mask(2))) ? 1u : 0u, ~(far[1] ^ up_mask(1))),
+            ~(far[0] ^ up_mask(0)));
+        E.x = lane(far[0]) ? E.x : Em.x;
+        E.y = lane(far[1]) ? E.y : Em.y;
+        E.z = lane(far[2]) ? E.z : Em.z;
+        lw -= 1u;
+        // (inside the pool for every validated pool; clamped, so that no other
+        // one reads past it)
+        I = __builtin_elementwise_min(r.x + oct, v.n_nodes - 1u);
+        r = ld_rec_t<SMALL>(rec, I);
+        pay = ld_pay_t<SMALL>(payp, I);
+        // waits for the record here, so that an iteration without a descent
+        // does not wait (for its payload) at the top of the loop
+        r.x = opaque(r.x);
+        if (STATS) acc.descent++;
+      }
+    }
+    if (need64 && !stop) {
       // FP64 rebase at the near face (axis bit kbe) of the current cell
-      const int kr = kbe == 0u ? 0 : __builtin_ctz(kbe);
-      const uint32_t cr = get(c, kr) ^ (get(up, kr) ? 0u : ~0u);  // true index
-      const double Xp = (double)(get(up, kr) ? cr : cr + 1u) * ldexp(1.0, -(int)dep);
+      const int kr = __builtin_ctz(kbe);
+      const double Xp = plane(kr, (int32_t)(1u << lw));
       const double te = (Xp - slot.at(kr)) * slot.at(6 + kr);
       for (int k = 0; k < 3; ++k) set(q, k, k == kr ? Xp : slot.at(k) + te * slot.at(3 + k));
-      rebase(te);
+      rebase(te, stop);
+    }
+    if (stop) {
+      if constexpr (!REFILL) break;
+      finish();
+      write_pixel();
+      alive = false;
     }
   }
   if constexpr (!REFILL) {
@@ -1018,8 +1027,8 @@ __device__ void cast_fp64(const DView& v, const V3<double>& d, const V3<double>&
     set(c, kx, mv.nc);
     I = mv.N;
     r = ld_rec(rec, I);
-    if (r.x & 1u) {
-      const uint32_t dL = (r.x >> 1) & 63u;
+    if (is_leaf(r.x)) {
+      const uint32_t dL = leaf_depth(r.x);
       const uint32_t m = dL < dep ? dep - dL : 0u;
       for (int k = 0; k < 3; ++k) set(c, k, get(c, k) >> m);
       dep -= m;
@@ -1107,8 +1116,8 @@ __device__ void cast_naive(const DView& v, const V3<double>& d, const Entry& en,
     set(c, kx, mv.nc);
     I = mv.N;
     r = ld_rec(rec, I);
-    if (r.x & 1u) {
-      const uint32_t dL = (r.x >> 1) & 63u;
+    if (is_leaf(r.x)) {
+      const uint32_t dL = leaf_depth(r.x);
       const uint32_t m = dL < dep ? dep - dL : 0u;
       for (int k = 0; k < 3; ++k) set(c, k, get(c, k) >> m);
       dep -= m;
@@ -1226,9 +1235,9 @@ __device__ void cast_local(const DView& v, const V3<double>& d, const Entry& en,
     set(c, kx, mv.nc);
     I = mv.N;
     r = ld_rec(rec, I);
-    if (r.x & 1u) {
+    if (is_leaf(r.x)) {
       // a coarser leaf: scale by 2^-m after the offset of the finer cell in it
-      const uint32_t dL = (r.x >> 1) & 63u;
+      const uint32_t dL = leaf_depth(r.x);
       const uint32_t m = dL < dep ? dep - dL : 0u;
       const float sc = ldexpf(1.0f, -(int)m);
       const uint32_t mask = (1u << m) - 1u;
@@ -1244,7 +1253,7 @@ __device__ void cast_local(const DView& v, const V3<double>& d, const Entry& en,
     } else {
       // a refined cell: children by the sign of p, ties to the side the ray moves into
       const uint32_t d0 = dep;
-      while (!(r.x & 1u)) {
+      while (!is_leaf(r.x)) {
         if (r.x >= v.n_nodes - 7u) { bad = true; break; }
         uint32_t oct = 0;
         for (int k = 0; k < 3; ++k) {

@@ -11,7 +11,24 @@
 #define CVX_NONE 0xffffffffu
 #define CVX_FREE 0xffffffffu  // record word x of a node that is not in the tree
 
+#define CVX_XLEAF 0x80000000u  // record word x of a leaf, or-ed with its depth
+
 namespace cvx {
+
+#ifdef __HIP__
+#define CVX_HD __host__ __device__
+#else
+#define CVX_HD
+#endif
+// Record words x (see below): CVX_FREE reads as a leaf too.
+CVX_HD inline bool is_leaf(uint32_t x) { return (int32_t)x < 0; }
+CVX_HD inline uint32_t leaf_depth(uint32_t x) { return x & 63u; }
+CVX_HD inline uint32_t public_x(uint32_t x) {
+  return x == CVX_FREE || !is_leaf(x) ? x : 1u | (leaf_depth(x) << 1);
+}
+CVX_HD inline uint32_t device_x(uint32_t x) {  // the inverse
+  return x == CVX_FREE || !(x & 1u) ? x : CVX_XLEAF | (x >> 1);
+}
 
 // Breadth-first order of the reachable nodes, one range per level.
 struct PoolPlan {
@@ -27,7 +44,11 @@ int validate_views(const cvx_view* views, int n_views, const cvx_canvas_desc* co
                    int n_canvases, std::string& msg);
 
 // Device node record (16 bytes), one per pool node, indexed like the input:
-//   x: leaf -> 1 | depth << 1 ; refined -> index of the first child (multiple of 8, even)
+//   x: leaf -> CVX_XLEAF | depth (the sign bit: one compare tells a leaf, one
+//      subtraction gives its width); refined -> index of the first child (a
+//      multiple of 8, below 2^31); CVX_FREE for an id not in the tree.  The
+//      host mirror and cvx_read_records hold x in its public form, a leaf as
+//      1 | depth << 1.
 //   y, z, w: outer-face neighbour on the x, y, z axis: the cell of the same
 //            depth across the face of the parent that this child touches, or
 //            the coarser leaf covering it; CVX_NONE outside the canvas or for roots.

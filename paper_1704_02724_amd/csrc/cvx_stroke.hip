@@ -119,9 +119,9 @@ __global__ void k_stroke_visit(const StrokeItem* __restrict__ items, uint32_t n,
     // a refined cell whose 8 children are leaves with identical payloads is
     // listed (with its first child's payload); otherwise its children are
     // looked at on the next level
-    if ((x & 1u) || (uint64_t)x + 8 > n_nodes) return;
+    if (is_leaf(x) || (uint64_t)x + 8 > n_nodes) return;
     bool uni = true;
-    for (uint32_t o = 0; o < 8; ++o) uni = uni && (rec[x + o].x & 1u);
+    for (uint32_t o = 0; o < 8; ++o) uni = uni && is_leaf(rec[x + o].x);
     if (uni) {
       if (a.fmt == CVX_LEAF_F64) {
         const double* p0 = (const double*)pay + 4 * (uint64_t)x;
@@ -153,7 +153,7 @@ __global__ void k_stroke_visit(const StrokeItem* __restrict__ items, uint32_t n,
       return;
     }
   }
-  if (!(x & 1u)) {
+  if (!is_leaf(x)) {
     if ((uint64_t)x + 8 > n_nodes) return;
     const uint32_t slot = atomicAdd(next_count, 8u);
     if (slot + 8 > next_cap) return;  // the host sees the count above the capacity

@@ -45,7 +45,7 @@ __global__ void k_relayout_level(const uint32_t* __restrict__ order, uint64_t be
   uint4 r;
   if (nd.x & CVX_LEAF_BIT) {
     uint32_t li = nd.x & ~CVX_LEAF_BIT;
-    r.x = 1u | (level << 1);
+    r.x = CVX_XLEAF | level;
     if (fmt == CVX_LEAF_RGBA8_F16) {
       ((uint2*)pay)[I] = ((const uint2*)raw_leaves)[li];
     } else {
@@ -64,7 +64,7 @@ __global__ void k_relayout_level(const uint32_t* __restrict__ order, uint64_t be
       uint32_t M = neighbour_of_parent(rec, P, level - 1, k, (o >> k) & 1u, R);
       if (M != CVX_NONE) {
         uint32_t mx = rec[M].x;
-        if (!(mx & 1u)) M = mx + (o ^ (1u << k));
+        if (!is_leaf(mx)) M = mx + (o ^ (1u << k));
       }
       link[k] = M;
     }
@@ -90,7 +90,7 @@ __global__ void k_top_table(const uint4* __restrict__ rec, uint64_t n_nodes, uin
   uint32_t I = (x >> L) + R * ((y >> L) + R * (z >> L));
   for (uint32_t lvl = 0; lvl < L; ++lvl) {
     const uint32_t cx = rec[I].x;
-    if ((cx & 1u) || (uint64_t)cx + 8 > n_nodes) break;
+    if (is_leaf(cx) || (uint64_t)cx + 8 > n_nodes) break;
     const uint32_t sh = L - 1 - lvl;
     I = cx + (((x >> sh) & 1u) | (((y >> sh) & 1u) << 1) | (((z >> sh) & 1u) << 2));
   }
@@ -107,10 +107,11 @@ int launch_top_table(void* stream, const void* rec, uint64_t n_nodes, uint32_t R
 }
 
 // ---- pool edits -------------------------------------------------------------
-// Record words x of nodes [0, n), packed (for the host mirror).
+// Record words x of nodes [0, n) in their public form, packed (for the host
+// mirror).
 __global__ void k_extract_x(const uint4* __restrict__ rec, uint64_t n, uint32_t* __restrict__ out) {
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = rec[i].x;
+  if (i < n) out[i] = public_x(rec[i].x);
 }
 
 int launch_extract_x(void* stream, const void* rec, uint64_t n, uint32_t* out) {
@@ -121,7 +122,8 @@ int launch_extract_x(void* stream, const void* rec, uint64_t n, uint32_t* out) {
   return (int)hipGetLastError();
 }
 
-// Record words x of touched nodes (first child, 1 | depth << 1, or CVX_FREE).
+// Record words x of touched nodes (first child, 1 | depth << 1, or CVX_FREE, as
+// the host mirror holds them).
 // A node that stays in the tree keeps its links (they depend on its parent,
 // which did not change); a node leaving the tree gets null links.
 __global__ void k_scatter_records(const uint32_t* __restrict__ ids, const uint32_t* __restrict__ xs,
@@ -132,7 +134,7 @@ __global__ void k_scatter_records(const uint32_t* __restrict__ ids, const uint32
   if (x == CVX_FREE)
     rec[ids[i]] = make_uint4(CVX_FREE, CVX_NONE, CVX_NONE, CVX_NONE);
   else
-    ((uint32_t*)&rec[ids[i]])[0] = x;
+    ((uint32_t*)&rec[ids[i]])[0] = device_x(x);
 }
 
 // Payloads of touched leaves, lb bytes each (8 or 32, so whole uint2 words).
@@ -160,7 +162,7 @@ __global__ void k_links_level(const uint32_t* __restrict__ frontier, uint64_t n,
   // as a root of a changed region) is processed once
   if (mark && atomicExch(&mark[P], epoch) == epoch) return;
   const uint32_t first = rec[P].x;
-  if ((first & 1u) || (uint64_t)first + 8 > n_nodes) return;
+  if (is_leaf(first) || (uint64_t)first + 8 > n_nodes) return;
   for (uint32_t o = 0; o < 8; ++o) {
     const uint32_t C = first + o;
     uint32_t link[3];
@@ -168,7 +170,7 @@ __global__ void k_links_level(const uint32_t* __restrict__ frontier, uint64_t n,
       uint32_t M = neighbour_of_parent(rec, P, level, k, (o >> k) & 1u, R);
       if (M != CVX_NONE) {
         const uint32_t mx = rec[M].x;
-        if (!(mx & 1u)) M = mx + (o ^ (1u << k));
+        if (!is_leaf(mx)) M = mx + (o ^ (1u << k));
       }
       link[k] = M;
     }
@@ -176,7 +178,7 @@ __global__ void k_links_level(const uint32_t* __restrict__ frontier, uint64_t n,
     w[1] = link[0];
     w[2] = link[1];
     w[3] = link[2];
-    if (!(rec[C].x & 1u)) next[atomicAdd(next_count, 1u)] = C;
+    if (!is_leaf(rec[C].x)) next[atomicAdd(next_count, 1u)] = C;
   }
 }
 
@@ -216,7 +218,7 @@ __global__ void k_dirty_roots(const uint32_t* __restrict__ changed,
     const uint32_t N = cand[j];
     if (N == CVX_NONE || (uint64_t)N >= n_nodes) continue;
     const uint32_t x = rec[N].x;
-    if (x == CVX_FREE || (x & 1u)) continue;
+    if (is_leaf(x)) continue;  // or not in the tree (CVX_FREE)
     const uint32_t slot = atomicAdd(out_count, 1u);
     out[slot] = N;
     out_depth[slot] = d;
