@@ -470,6 +470,7 @@ int render_launch(cvx_ctx* ctx, const cvx_view* views, int n_views, void* out_de
   H.n_rays = rows;
   H.n_views = (uint32_t)n_views;
   H.n_queues = o.single_queue ? 1u : cvx::CVX_NQ;
+  H.drained = 0;
   for (auto& q : H.queue) q.next = 0;
   if (H.total_work >= (1ull << 32)) return fail(ctx, CVX_ERR_INVALID_ARG, "too much work in one call");
   // one transfer; it also zeroes the queue heads for this call
@@ -502,6 +503,11 @@ int render_launch(cvx_ctx* ctx, const cvx_view* views, int n_views, void* out_de
     a.trace_rgba = tr->rgba;
     a.end_point = tr->end_point;
   }
+  // no more workgroups than there are work items for, to the next power of two
+  // (a captured graph then serves view sets of about the same size)
+  uint64_t want = 8;
+  while (want * (p.wg / 64u) < H.total_work) want *= 2;
+  const uint32_t wgs = (uint32_t)std::min<uint64_t>(p.wgs, want);
   const bool stats = o.stats != nullptr;
   const uint32_t shared_start = o.per_ray_start ? 0u : 1u;
   // a split render writes its pieces to the context's buffer, merged after
@@ -533,7 +539,7 @@ int render_launch(cvx_ctx* ctx, const cvx_view* views, int n_views, void* out_de
     if (le != hipSuccess) return hip_fail(ctx, (hipError_t)le, "k_view_starts");
     const hipEvent_t* ev = (const hipEvent_t*)o.cast_events;
     if (ev) CVX_HIP(hipEventRecord(ev[0], ctx->stream));
-    le = cvx::launch_cast(ctx->stream, o.variant, tr != nullptr, stats, o.out_f64 != 0, a, p.wgs,
+    le = cvx::launch_cast(ctx->stream, o.variant, tr != nullptr, stats, o.out_f64 != 0, a, wgs,
                           p.wg);
     if (le != hipSuccess) return hip_fail(ctx, (hipError_t)le, "k_cast");
     if (ev) CVX_HIP(hipEventRecord(ev[1], ctx->stream));
@@ -548,7 +554,7 @@ int render_launch(cvx_ctx* ctx, const cvx_view* views, int n_views, void* out_de
   key.variant = o.variant;
   key.tw = p.tw;
   key.th = p.th;
-  key.wgs = p.wgs;
+  key.wgs = wgs;
   key.wg = p.wg;
   key.item_tiles = p.item_tiles;
   key.refill_min = p.refill_min;
@@ -567,7 +573,7 @@ int render_launch(cvx_ctx* ctx, const cvx_view* views, int n_views, void* out_de
     CVX_HIP(hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal));
     int le = cvx::launch_view_starts(ctx->stream, st.d_views, st.d_hdr, shared_start);
     if (le == hipSuccess)
-      le = cvx::launch_cast(ctx->stream, o.variant, false, stats, o.out_f64 != 0, a, p.wgs, p.wg);
+      le = cvx::launch_cast(ctx->stream, o.variant, false, stats, o.out_f64 != 0, a, wgs, p.wg);
     if (le == hipSuccess && merge)
       le = cvx::launch_merge_pieces(ctx->stream, st.d_views, st.d_hdr, (uint32_t)n_views,
                                     ctx->d_split, out_dev, p.pieces);

@@ -144,10 +144,11 @@ struct DView {
 // CVX_NQ contiguous ranges, one per XCD (a workgroup runs on XCD
 // blockIdx.x mod 8), so the tiles one XCD renders are neighbours and share
 // its L2.  A wavefront drains its own range first, then the others in turn.
-constexpr uint32_t CVX_NQ = 8;
+constexpr uint32_t CVX_NQ_LOG = 3;
+constexpr uint32_t CVX_NQ = 1u << CVX_NQ_LOG;
 
 struct alignas(128) QueueHead {
-  uint32_t next;  // items taken from this range so far
+  uint32_t next;  // items taken from this range past the fixed ones
   uint32_t pad[31];
 };
 
@@ -158,7 +159,8 @@ struct CastHeader {
   uint64_t n_rays;      // trace mode: number of listed rays
   uint32_t n_views;
   uint32_t n_queues;        // 1 or CVX_NQ ranges in use
-  uint32_t pad[26];
+  uint32_t drained;         // bit q: range q was found exhausted
+  uint32_t pad[25];
   QueueHead queue[CVX_NQ];  // reset by a kernel before each cast
 };
 
