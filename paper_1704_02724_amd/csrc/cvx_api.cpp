@@ -21,7 +21,8 @@ using cvx::DView;
 struct GraphKey {
   uint32_t variant = ~0u, tw = 0, th = 0, wgs = 0, wg = 0, item_tiles = 1, refill_min = 0,
            pieces = 1;
-  bool trace = false, stats = false, out64 = false, small = false, per_ray_start = false;
+  bool trace = false, stats = false, out64 = false, small = false, per_ray_start = false,
+       by_args = false;
   const void* out = nullptr;
   const void* stats_ptr = nullptr;
   const void* views = nullptr;
@@ -31,7 +32,7 @@ struct GraphKey {
            item_tiles == o.item_tiles && refill_min == o.refill_min && pieces == o.pieces &&
            split_tmp == o.split_tmp &&
            trace == o.trace && stats == o.stats && out64 == o.out64 && small == o.small &&
-           per_ray_start == o.per_ray_start &&
+           per_ray_start == o.per_ray_start && by_args == o.by_args &&
            out == o.out && stats_ptr == o.stats_ptr && views == o.views;
   }
 };
@@ -413,9 +414,15 @@ struct RenderStage {
   const char* split_why;   // the error otherwise
 };
 
-// Fills the staged views and header, copies them to the device and launches
-// the view-start, queue-reset and cast kernels, eagerly or through the
-// context's graph.
+// Calls of up to this many views pass them as kernel arguments, 16 a launch of
+// 4-9 us; larger tables are copied.  A call's time outside its cast kernel,
+// copied / as arguments: 45 / 35 us with 1 view, 34 / 36 with 48 views (3
+// launches), 61 / 79 with 64 (4 launches, each with eyes to locate).
+constexpr uint32_t kStageArgViews = 2 * cvx::CVX_STAGE_VIEWS;
+
+// Fills the staged views and header, brings them to the device (with each
+// view's start leaf and the queue reset) and launches the cast kernel, eagerly
+// or through the context's graph.
 int render_launch(cvx_ctx* ctx, const cvx_view* views, int n_views, void* out_dev,
                   const cvx_render_opts& o, const RenderPlan& p, const RenderStage& st) {
   const cvx_trace* tr = o.trace;
@@ -473,11 +480,19 @@ int render_launch(cvx_ctx* ctx, const cvx_view* views, int n_views, void* out_de
   H.drained = 0;
   for (auto& q : H.queue) q.next = 0;
   if (H.total_work >= (1ull << 32)) return fail(ctx, CVX_ERR_INVALID_ARG, "too much work in one call");
-  // one transfer; it also zeroes the queue heads for this call
-  CVX_HIP(hipMemcpyAsync(st.d_hdr, st.h_hdr, sizeof(CastHeader) + sizeof(DView) * n_views,
-                         hipMemcpyHostToDevice, ctx->stream));
-  CVX_HIP(hipEventRecord(st.staged, ctx->stream));
-  *st.staged_pending = true;
+  const uint32_t shared_start = o.per_ray_start ? 0u : 1u;
+  const bool by_args = (uint32_t)n_views <= kStageArgViews;
+  if (by_args) {
+    int le = cvx::launch_stage_views(ctx->stream, st.h_views, (uint32_t)n_views, H, st.d_views,
+                                     st.d_hdr, shared_start);
+    if (le != hipSuccess) return hip_fail(ctx, (hipError_t)le, "k_stage_views");
+  } else {
+    // one transfer; it also zeroes the queue heads for this call
+    CVX_HIP(hipMemcpyAsync(st.d_hdr, st.h_hdr, sizeof(CastHeader) + sizeof(DView) * n_views,
+                           hipMemcpyHostToDevice, ctx->stream));
+    CVX_HIP(hipEventRecord(st.staged, ctx->stream));
+    *st.staged_pending = true;
+  }
 
   CastArgs a{};
   a.views = st.d_views;
@@ -509,7 +524,6 @@ int render_launch(cvx_ctx* ctx, const cvx_view* views, int n_views, void* out_de
   while (want * (p.wg / 64u) < H.total_work) want *= 2;
   const uint32_t wgs = (uint32_t)std::min<uint64_t>(p.wgs, want);
   const bool stats = o.stats != nullptr;
-  const uint32_t shared_start = o.per_ray_start ? 0u : 1u;
   // a split render writes its pieces to the context's buffer, merged after
   bool merge = false;
   if (!tr && p.pieces > 1) {
@@ -535,7 +549,8 @@ int render_launch(cvx_ctx* ctx, const cvx_view* views, int n_views, void* out_de
   }
   a.split_tmp = merge ? ctx->d_split : nullptr;
   if (!o.use_graph || tr) {
-    int le = cvx::launch_view_starts(ctx->stream, st.d_views, st.d_hdr, shared_start);
+    int le = hipSuccess;
+    if (!by_args) le = cvx::launch_view_starts(ctx->stream, st.d_views, st.d_hdr, shared_start);
     if (le != hipSuccess) return hip_fail(ctx, (hipError_t)le, "k_view_starts");
     const hipEvent_t* ev = (const hipEvent_t*)o.cast_events;
     if (ev) CVX_HIP(hipEventRecord(ev[0], ctx->stream));
@@ -565,13 +580,15 @@ int render_launch(cvx_ctx* ctx, const cvx_view* views, int n_views, void* out_de
   key.out64 = o.out_f64 != 0;
   key.small = a.small_pools != 0;
   key.per_ray_start = o.per_ray_start != 0;
+  key.by_args = by_args;
   key.out = out_dev;
   key.stats_ptr = o.stats;
   key.views = st.d_views;
   if (!ctx->gexec || !(key == ctx->gkey)) {
     drop_graph(ctx);
     CVX_HIP(hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal));
-    int le = cvx::launch_view_starts(ctx->stream, st.d_views, st.d_hdr, shared_start);
+    int le = hipSuccess;
+    if (!by_args) le = cvx::launch_view_starts(ctx->stream, st.d_views, st.d_hdr, shared_start);
     if (le == hipSuccess)
       le = cvx::launch_cast(ctx->stream, o.variant, false, stats, o.out_f64 != 0, a, wgs, p.wg);
     if (le == hipSuccess && merge)

@@ -27,6 +27,7 @@
 //                end of Sec. 6.3 argues would suffice.
 #include <hip/hip_runtime.h>
 
+#include <cstring>
 #include <mutex>
 
 #include "cvx_internal.h"
@@ -1632,19 +1633,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void k
   cast_grid<(int)CVX_VARIANT_FP64_PLAIN, TRACE, STATS, OUT64>(a);
 }
 
-// One thread per view: the leaf holding the eye, when every ray of the view
-// starts there (eye strictly inside the canvas and off every plane of the
-// deepest grid: the slab test then gives t0 = 0 and the start point is the
-// eye itself for every direction).  The first CVX_NQ threads also clear the
-// work-queue heads (the staged header arrives with them at zero; a cleared
-// head keeps a replayed launch safe on its own).
-__global__ void k_view_starts(DView* views, CastHeader* hdr, uint32_t enable) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < CVX_NQ) hdr->queue[i].next = 0u;
-  if (i == 0) hdr->drained = 0u;
-  if (i >= hdr->n_views) return;  // the count of this call (a graph replays the launch)
-  DView& v = views[i];
-  v.start_ok = 0u;
+// The leaf holding the eye of view v, into dst (v's place in the device
+// table), when every ray of the view starts there (eye strictly inside the
+// canvas and off every plane of the deepest grid: the slab test then gives
+// t0 = 0 and the start point is the eye itself for every direction).
+__device__ __forceinline__ void view_start(const DView& v, DView& dst, uint32_t enable) {
+  dst.start_ok = 0u;
   if (!enable) return;
   const double Rd = (double)v.R;
   bool ok = true;
@@ -1661,12 +1655,50 @@ __global__ void k_view_starts(DView* views, CastHeader* hdr, uint32_t enable) {
   uint4 r;
   locate_top(v, C, I, dep, c, r);
   if (!descend_int(v.rec, v.n_nodes, C, v.max_depth, I, dep, c, r)) return;
-  v.start_node = I;
-  v.start_dep = dep;
-  v.start_c[0] = c.x;
-  v.start_c[1] = c.y;
-  v.start_c[2] = c.z;
-  v.start_ok = 1u;
+  dst.start_node = I;
+  dst.start_dep = dep;
+  dst.start_c[0] = c.x;
+  dst.start_c[1] = c.y;
+  dst.start_c[2] = c.z;
+  dst.start_ok = 1u;
+}
+
+// View starts of a call whose table was copied to the device: one thread per
+// view.  The first CVX_NQ threads also clear the work-queue heads (the staged
+// header arrives with them at zero; a cleared head keeps a replayed launch
+// safe on its own).
+__global__ void k_view_starts(DView* views, CastHeader* hdr, uint32_t enable) {
+  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < CVX_NQ) hdr->queue[i].next = 0u;
+  if (i == 0) hdr->drained = 0u;
+  if (i >= hdr->n_views) return;  // the count of this call (a graph replays the launch)
+  view_start(views[i], views[i], enable);
+}
+
+// The same for a call of few views, which come as kernel arguments (up to
+// CVX_STAGE_VIEWS a launch): one block writes them, their starts and the
+// header.  A copy from pinned host memory, the event that guards the host
+// side and the gaps between them cost about 10 us more per call (a 64x64 view:
+// 119 / 110 us, a 2160x2160 stereo pair 465 / 452) and made the host wait for
+// the previous call's copy.
+__global__ __launch_bounds__(256) void k_stage_views(StageViews s, DView* views, CastHeader* hdr,
+                                                     uint32_t enable) {
+  const uint32_t t = threadIdx.x;
+  if (s.first == 0u) {
+    if (t < CVX_NQ) hdr->queue[t].next = 0u;
+    if (t == 0) {
+      hdr->drained = 0u;
+      hdr->total_work = s.total_work;
+      hdr->n_rays = s.n_rays;
+      hdr->n_views = s.n_views;
+      hdr->n_queues = s.n_queues;
+    }
+  }
+  const uint32_t* src = (const uint32_t*)s.v;
+  uint32_t* dst = (uint32_t*)(views + s.first);
+  for (uint32_t w = t; w < s.count * (uint32_t)(sizeof(DView) / 4); w += blockDim.x) dst[w] = src[w];
+  __syncthreads();
+  if (t < s.count) view_start(s.v[t], views[s.first + t], enable);
 }
 
 template <int VAR, bool TRACE, bool STATS, bool OUT64>
@@ -1751,6 +1783,28 @@ int launch_view_starts(void* stream, DView* views, CastHeader* hdr, uint32_t ena
   hipLaunchKernelGGL(k_view_starts, dim3((CVX_MAX_VIEWS + 63u) / 64u), dim3(64), 0,
                      (hipStream_t)stream, views, hdr, enable);
   return (int)hipGetLastError();
+}
+
+// Stages the views of a call through kernel arguments (the host arrays are
+// read before it returns).
+int launch_stage_views(void* stream, const DView* host_views, uint32_t n_views,
+                       const CastHeader& host_hdr, DView* views, CastHeader* hdr,
+                       uint32_t enable) {
+  StageViews s;
+  s.total_work = host_hdr.total_work;
+  s.n_rays = host_hdr.n_rays;
+  s.n_views = host_hdr.n_views;
+  s.n_queues = host_hdr.n_queues;
+  for (uint32_t i = 0; i < n_views; i += CVX_STAGE_VIEWS) {
+    s.first = i;
+    s.count = n_views - i < CVX_STAGE_VIEWS ? n_views - i : CVX_STAGE_VIEWS;
+    std::memcpy(s.v, host_views + i, s.count * sizeof(DView));
+    hipLaunchKernelGGL(k_stage_views, dim3(1), dim3(256), 0, (hipStream_t)stream, s, views, hdr,
+                       enable);
+    const int e = (int)hipGetLastError();
+    if (e != (int)hipSuccess) return e;
+  }
+  return (int)hipSuccess;
 }
 
 int launch_merge_pieces(void* stream, const DView* views, const CastHeader* hdr, uint32_t n_views,

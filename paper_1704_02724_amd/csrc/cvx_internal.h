@@ -164,6 +164,16 @@ struct CastHeader {
   QueueHead queue[CVX_NQ];  // reset by a kernel before each cast
 };
 
+// Views of a call passed as kernel arguments (at most 4 KB a launch).
+constexpr uint32_t CVX_STAGE_VIEWS = 16;
+struct StageViews {
+  uint64_t total_work, n_rays;  // the call's header
+  uint32_t n_views, n_queues;
+  uint32_t first, count;        // the views of this launch
+  DView v[CVX_STAGE_VIEWS];
+};
+static_assert(sizeof(StageViews) <= 4000, "kernel arguments are limited to 4 KB");
+
 struct CastArgs {
   const DView* views;
   CastHeader* hdr;
@@ -225,6 +235,11 @@ constexpr size_t CVX_SCRATCH_BYTES = sizeof(CastHeader) + CVX_NOALLOC_MAX_VIEWS 
 int scratch_address(int device, void** ptr);
 // the shared first leaf of every view whose eye lies inside its canvas
 int launch_view_starts(void* stream, DView* views, CastHeader* hdr, uint32_t enable);
+// the same for views passed as kernel arguments, which it also writes to the
+// device table together with the header
+int launch_stage_views(void* stream, const DView* host_views, uint32_t n_views,
+                       const CastHeader& host_hdr, DView* views, CastHeader* hdr,
+                       uint32_t enable);
 // one level of a stroke's walk (cvx_stroke.hip); items == nullptr: the roots;
 // merge = 1: find cells to merge instead of painting and splitting
 int launch_stroke_visit(void* stream, const StrokeItem* items, uint32_t n, const StrokeArgs& a,
