@@ -31,8 +31,8 @@
  *
  * Errors: every entry point returns CVX_OK (0) or a negative CVX_ERR_* code;
  * no C++ exception crosses this boundary.  A failed call leaves previously
- * uploaded pools unchanged.  A context is bound to one HIP device and one
- * stream and is not thread-safe.
+ * uploaded pools unchanged.  A context is bound to one HIP device and, at a
+ * time, one stream, and is not thread-safe.
  */
 #ifndef CVX_H
 #define CVX_H
@@ -217,6 +217,14 @@ typedef struct {
  * index out of range, CVX_ERR_HIP if the runtime fails, CVX_ERR_OOM if the
  * host allocation fails; *ctx is NULL on failure. */
 int cvx_create(cvx_ctx** ctx, int hip_device, void* hip_stream);
+
+/* Enqueue the context's further calls on hip_stream (borrowed; NULL = the null
+ * stream) instead of the stream it was on, after what it enqueued there (no
+ * wait is inserted when hip_stream is being captured).  A caller that renders
+ * on the stream its other work is on needs no events between the two, which
+ * cost about 20 us a frame.  Graphs (use_graph) stay available as the stream
+ * given to cvx_create had it. */
+int cvx_set_stream(cvx_ctx* ctx, void* hip_stream);
 
 /* Upload a canvas pool (Sec. 4.1.1-4.1.2): host arrays are read during the
  * call only.  The pool is validated (indices in range, children groups

@@ -39,7 +39,9 @@ struct GraphKey {
 
 struct cvx_ctx {
   int device = 0;
-  hipStream_t stream = nullptr;
+  hipStream_t stream = nullptr;   // the stream calls enqueue on (cvx_set_stream)
+  hipStream_t home = nullptr;     // the stream of cvx_create; graphs are captured on it
+  hipEvent_t moved{};             // orders a new stream after the one before it
   int n_cu = 256;
   std::string err;
   DevCanvas canvases[CVX_MAX_CANVASES];
@@ -160,7 +162,7 @@ int cvx_create(cvx_ctx** out, int hip_device, void* hip_stream) {
   cvx_ctx* ctx = new (std::nothrow) cvx_ctx();
   if (!ctx) return CVX_ERR_OOM;
   ctx->device = hip_device;
-  ctx->stream = (hipStream_t)hip_stream;
+  ctx->stream = ctx->home = (hipStream_t)hip_stream;
   hipError_t e = hipSetDevice(hip_device);
   hipDeviceProp_t prop;
   if (e == hipSuccess) e = hipGetDeviceProperties(&prop, hip_device);
@@ -176,6 +178,7 @@ int cvx_create(cvx_ctx** out, int hip_device, void* hip_stream) {
   if (e == hipSuccess) e = (hipError_t)cvx::scratch_address(hip_device, &ctx->d_scratch);
   if (e == hipSuccess) e = hipHostMalloc(&ctx->h_scratch, cvx::CVX_SCRATCH_BYTES, 0);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->scratch_staged, hipEventDisableTiming);
+  if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->moved, hipEventDisableTiming);
   if (e != hipSuccess) {
     cvx_destroy(ctx);
     return CVX_ERR_HIP;
@@ -187,7 +190,11 @@ int cvx_create(cvx_ctx** out, int hip_device, void* hip_stream) {
 void cvx_destroy(cvx_ctx* ctx) {
   if (!ctx) return;
   (void)hipSetDevice(ctx->device);
-  (void)hipStreamSynchronize(ctx->stream);
+  // (a stream the caller has destroyed since: wait for the device instead)
+  if (hipStreamSynchronize(ctx->stream) != hipSuccess) {
+    (void)hipGetLastError();
+    (void)hipDeviceSynchronize();
+  }
   drop_graph(ctx);
   for (auto& c : ctx->canvases) free_canvas(c);
   if (ctx->d_stage) (void)hipFree(ctx->d_stage);
@@ -196,7 +203,31 @@ void cvx_destroy(cvx_ctx* ctx) {
   if (ctx->staged) (void)hipEventDestroy(ctx->staged);
   if (ctx->h_scratch) (void)hipHostFree(ctx->h_scratch);
   if (ctx->scratch_staged) (void)hipEventDestroy(ctx->scratch_staged);
+  if (ctx->moved) (void)hipEventDestroy(ctx->moved);
   delete ctx;
+}
+
+int cvx_set_stream(cvx_ctx* ctx, void* hip_stream) {
+  if (!ctx) return CVX_ERR_INVALID_ARG;
+  ctx->err.clear();
+  const hipStream_t to = (hipStream_t)hip_stream;
+  if (to == ctx->stream) return CVX_OK;
+  CVX_HIP(hipSetDevice(ctx->device));
+  // what the context enqueued on the old stream comes first.  A stream being
+  // captured cannot wait for work outside its capture: there the caller has
+  // synchronised before.
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (to) CVX_HIP(hipStreamIsCapturing(to, &cap));
+  if (cap == hipStreamCaptureStatusNone) {
+    hipError_t e = hipEventRecord(ctx->moved, ctx->stream);
+    if (e == hipSuccess) e = hipStreamWaitEvent(to, ctx->moved, 0);
+    if (e != hipSuccess) {  // the old stream was destroyed
+      (void)hipGetLastError();
+      CVX_HIP(hipDeviceSynchronize());
+    }
+  }
+  ctx->stream = to;
+  return CVX_OK;
 }
 
 int cvx_upload_pool(cvx_ctx* ctx, int canvas_id, const cvx_canvas_desc* desc,
@@ -380,7 +411,7 @@ int render_check(cvx_ctx* ctx, const cvx_view* views, int n_views, const void* o
   } else if (!out_dev) {
     return fail(ctx, CVX_ERR_INVALID_ARG, "out_dev is NULL");
   }
-  if (o.use_graph && !ctx->stream)
+  if (o.use_graph && !ctx->home)
     return fail(ctx, CVX_ERR_INVALID_ARG, "use_graph needs a non-null stream");
   if (o.cast_events && o.use_graph)
     return fail(ctx, CVX_ERR_INVALID_ARG, "cast_events are recorded by eager launches only");
@@ -586,16 +617,16 @@ int render_launch(cvx_ctx* ctx, const cvx_view* views, int n_views, void* out_de
   key.views = st.d_views;
   if (!ctx->gexec || !(key == ctx->gkey)) {
     drop_graph(ctx);
-    CVX_HIP(hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal));
+    CVX_HIP(hipStreamBeginCapture(ctx->home, hipStreamCaptureModeThreadLocal));
     int le = hipSuccess;
-    if (!by_args) le = cvx::launch_view_starts(ctx->stream, st.d_views, st.d_hdr, shared_start);
+    if (!by_args) le = cvx::launch_view_starts(ctx->home, st.d_views, st.d_hdr, shared_start);
     if (le == hipSuccess)
-      le = cvx::launch_cast(ctx->stream, o.variant, false, stats, o.out_f64 != 0, a, wgs, p.wg);
+      le = cvx::launch_cast(ctx->home, o.variant, false, stats, o.out_f64 != 0, a, wgs, p.wg);
     if (le == hipSuccess && merge)
-      le = cvx::launch_merge_pieces(ctx->stream, st.d_views, st.d_hdr, (uint32_t)n_views,
+      le = cvx::launch_merge_pieces(ctx->home, st.d_views, st.d_hdr, (uint32_t)n_views,
                                     ctx->d_split, out_dev, p.pieces);
     hipGraph_t g = nullptr;
-    hipError_t ee = hipStreamEndCapture(ctx->stream, &g);
+    hipError_t ee = hipStreamEndCapture(ctx->home, &g);
     if (le != hipSuccess) {
       if (g) (void)hipGraphDestroy(g);
       return hip_fail(ctx, (hipError_t)le, "graph capture launch");

@@ -55,7 +55,7 @@ EXPORTED = ["cvx_create", "cvx_upload_pool", "cvx_render", "cvx_free_pool", "cvx
             "cvx_last_error", "cvx_status_str", "cvx_validate_pool", "cvx_validate_views",
             "cvx_pool_bytes", "cvx_autotune", "cvx_edit_pool", "cvx_pool_nodes",
             "cvx_read_records", "cvx_read_payloads", "cvx_stroke_begin", "cvx_stroke_step",
-            "cvx_render_noalloc"]
+            "cvx_render_noalloc", "cvx_set_stream"]
 
 CVX_EDIT_PAINT = 0
 CVX_EDIT_REFINE = 1
@@ -139,6 +139,7 @@ _lib.cvx_upload_pool.argtypes = [_vp, ctypes.c_int, ctypes.POINTER(cvx_canvas_de
 _lib.cvx_render.argtypes = [_vp, _vp, ctypes.c_int, _vp, ctypes.POINTER(cvx_render_opts)]
 _lib.cvx_render_noalloc.argtypes = [_vp, _vp, ctypes.c_int, _vp,
                                     ctypes.POINTER(cvx_render_opts)]
+_lib.cvx_set_stream.argtypes = [_vp, _vp]
 _lib.cvx_free_pool.argtypes = [_vp, ctypes.c_int]
 _lib.cvx_destroy.argtypes = [_vp]
 _lib.cvx_destroy.restype = None
@@ -211,6 +212,11 @@ def cvx_create(device: int = 0, stream: int = 0):
     if rc != CVX_OK:
         raise CvxError(rc, "cvx_create failed")
     return h
+
+
+def cvx_set_stream(ctx, stream: int):
+    """Further calls of the context go to this stream (0: the null stream)."""
+    _check(ctx, _lib.cvx_set_stream(ctx, _vp(int(stream)) if stream else None))
 
 
 def cvx_upload_pool(ctx, canvas_id, desc, nodes, leaves):

@@ -21,9 +21,12 @@ class Session:
         torch.cuda.set_device(device)
         self.device = torch.device("cuda", device)
         # a stream of our own (default priority): graph capture needs a
-        # non-null stream; it is ordered against torch's current stream
-        self.stream = torch.cuda.Stream(self.device)
-        self.ctx = cvx.cvx_create(device, self.stream.cuda_stream)
+        # non-null stream.  Renders go to torch's current stream: through a
+        # stream of their own, ordered against it by two events, every frame
+        # cost about 20 us more (a 64x64 view: 95 us against 72)
+        self._home = torch.cuda.Stream(self.device)
+        self._bound = self._home
+        self.ctx = cvx.cvx_create(device, self._home.cuda_stream)
         self.descs = {}
 
     def close(self):
@@ -66,13 +69,22 @@ class Session:
         self.descs.pop(canvas_id, None)
 
     # -- stream ordering ----------------------------------------------------
+    @property
+    def stream(self):
+        """The session's own stream, ordered after every render so far."""
+        if self._bound != self._home:
+            self._home.wait_stream(self._bound)
+        return self._home
+
     def _enter(self):
-        self.stream.wait_stream(self.torch.cuda.current_stream(self.device))
+        cur = self.torch.cuda.current_stream(self.device)
+        if cur != self._bound:
+            cvx.cvx_set_stream(self.ctx, cur.cuda_stream)
+            self._bound = cur
 
     def _leave(self, *tensors):
-        self.torch.cuda.current_stream(self.device).wait_stream(self.stream)
-        for t in tensors:
-            t.record_stream(self.stream)
+        for t in tensors:  # one allocated on another stream lives until the render is done
+            t.record_stream(self._bound)
 
     # -- render -----------------------------------------------------------
     def out_pixels(self, views):
@@ -150,7 +162,6 @@ class Session:
         opts = cvx.make_opts(variant, trace=tr, chord_pieces=chord_pieces)
         self._enter()
         cvx.cvx_render(self.ctx, varr, 0, opts)
-        self._leave(ids, leaf_ids, llen, nl, fl, rgba, *([end] if end is not None else []))
         torch.cuda.synchronize(self.device)
         res = dict(leaf_ids=leaf_ids.cpu().numpy().view(np.uint32), local_len=llen.cpu().numpy(),
                    n_leaves=nl.cpu().numpy().view(np.uint32), flags=fl.cpu().numpy().view(np.uint32),
