@@ -363,6 +363,15 @@ struct RenderPlan {
                         // the canvas exit; 1: unsplit)
 };
 
+// Wavefronts of a call's cast kernel that one CU surely holds together: 8 per
+// SIMD of the FP32 render, 6 of the FP64 one (registers), 3 or more of the other
+// instances (trace, stats, comparison variants, lane refill).
+uint32_t resident_waves(const cvx_render_opts& o) {
+  if (o.trace || o.stats || o.rays_per_wave > 64u) return 12u;
+  if (o.variant == CVX_VARIANT_FP32_REBASED) return 32u;
+  return o.variant == CVX_VARIANT_FP64_PLAIN ? 24u : 12u;
+}
+
 // Checks the options and views of a render call (nothing is launched on an
 // error).
 int render_check(cvx_ctx* ctx, const cvx_view* views, int n_views, const void* out_dev,
@@ -554,6 +563,7 @@ int render_launch(cvx_ctx* ctx, const cvx_view* views, int n_views, void* out_de
   uint64_t want = 8;
   while (want * (p.wg / 64u) < H.total_work) want *= 2;
   const uint32_t wgs = (uint32_t)std::min<uint64_t>(p.wgs, want);
+  a.fixed_wgs = std::min<uint32_t>(wgs, (uint32_t)ctx->n_cu * (64u * resident_waves(o) / p.wg));
   const bool stats = o.stats != nullptr;
   // a split render writes its pieces to the context's buffer, merged after
   bool merge = false;

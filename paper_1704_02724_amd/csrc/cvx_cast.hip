@@ -35,6 +35,9 @@
 #ifndef CVX_CAST32_WAVES
 #define CVX_CAST32_WAVES 8
 #endif
+#ifndef CVX_CAST64_WAVES
+#define CVX_CAST64_WAVES 6
+#endif
 #ifndef CVX_CAST32R_WAVES
 #define CVX_CAST32R_WAVES 7
 #endif
@@ -410,6 +413,46 @@ __device__ __forceinline__ uint32_t opaque_s(uint32_t x) {
 __device__ __forceinline__ float kappa_of(uint2 p) {
   return (float)__builtin_bit_cast(_Float16, (unsigned short)(p.y & 0xffffu));
 }
+
+// Leaf payloads of the FP64 caster: RGBA8 + half kappa (colours accumulate as
+// bytes, divided by kScale once per ray) or four doubles.
+template <bool LEAF64>
+struct LeafLoad {
+  typedef uint2 type;
+  static constexpr double kScale = 255.0;
+  template <bool SMALL>
+  static __device__ __forceinline__ uint2 load(const void* pay, uint32_t i) {
+    return ld_pay_t<SMALL>(pay, i);
+  }
+  static __device__ __forceinline__ void decode(uint2 p, double& r, double& g, double& b,
+                                                double& kap) {
+    r = (double)(p.x & 0xffu);
+    g = (double)((p.x >> 8) & 0xffu);
+    b = (double)((p.x >> 16) & 0xffu);
+    kap = (double)kappa_of(p);
+  }
+};
+typedef double f64x2_t __attribute__((ext_vector_type(2)));
+typedef const __attribute__((address_space(1))) f64x2_t* gpay64_t;
+template <>
+struct LeafLoad<true> {
+  struct type {
+    f64x2_t rg, bk;
+  };
+  static constexpr double kScale = 1.0;
+  template <bool SMALL>
+  static __device__ __forceinline__ type load(const void* pay, uint32_t i) {
+    const gpay64_t p = (gpay64_t)pay + 2 * (uint64_t)i;
+    return type{p[0], p[1]};
+  }
+  static __device__ __forceinline__ void decode(const type& p, double& r, double& g, double& b,
+                                                double& kap) {
+    r = p.rg.x;
+    g = p.rg.y;
+    b = p.bk.x;
+    kap = p.bk.y;
+  }
+};
 
 // ----------------------------------------------------------------------------
 // FP32_REBASED: cell-local FP32 traversal (Sec. 6.1-6.2) as a certified DDA.
@@ -953,97 +996,162 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
 }
 
 // ----------------------------------------------------------------------------
-// FP64_PLAIN: canvas-global FP64; exit parameters from the exact face planes
-// ((integer + side) 2^-dep - o_k) / d_k every step, FP64 compositing.
+// FP64_PLAIN: canvas-global FP64.  The cell is held as in the FP32 caster (lw,
+// E_k); the exit parameter of each axis comes from its exact face plane every
+// step, (F - o_k) / |d_k| with F = E_k + 1 and o_k, |d_k| scaled to base cells
+// (a power of two: the roundings are those of (X - o) / d), FP64 compositing.
+// A refined cell is descended, one level in the iteration that entered it, by
+// comparing the mid-planes' parameters with the entry's.  The neighbour's
+// record is on its way during the composite and the payload from the move on.
+//
+// Bound by FP64 vector issue (an exponential per leaf) and latency.  Against
+// plane positions built from cell indices, three divisions by 255 per leaf,
+// payloads loaded where they were used and a descent loop inside the step
+// (whole call, before / after): 960x540 stereo, 17 M nodes, 585 / 316 us; a
+// 256x256 view of FP64 leaves 190 / 114 us.  76 VGPRs: 6 wavefronts per SIMD
+// without spills (7 would spill 24 bytes per lane).
 // ----------------------------------------------------------------------------
-template <bool TRACE, bool STATS>
+template <bool TRACE, bool STATS, bool SMALL, bool LEAF64>
 __device__ void cast_fp64(const DView& v, const V3<double>& d, const V3<double>& inv,
                           const Entry& en, const V3<bool>& up, Sink sk, Acc& acc, Out& out) {
-  const V3<double> o{v.o[0], v.o[1], v.o[2]};
   const double Rd = (double)v.R;
   const void* rec = v.rec;
+  const uint32_t D = v.max_depth;
   const bool use_stop = v.alpha_stop < 1.0f;
   V3<double> q;
+  V3<double> os, is;        // the eye along the ray's direction, 1 / |d|; base cells
+  uint64_t upm[3], parm = 0;
   for (int k = 0; k < 3; ++k) {
-    double qk = get(o, k) + en.t0 * get(d, k);
+    const double ok = v.o[k], dk = get(d, k);
+    double qk = ok + en.t0 * dk;
     if (k == en.kin) qk = en.side ? Rd : 0.0;
     set(q, k, qk < 0.0 ? 0.0 : (qk > Rd ? Rd : qk));
+    // a ray parallel to the axis never reaches its planes: t = inf
+    const bool par = dk == 0.0;
+    set(os, k, par ? -__builtin_inf() : ldexp(get(up, k) ? ok : -ok, (int)D));
+    set(is, k, par ? 1.0 : ldexp(__builtin_fabs(get(inv, k)), -(int)D));
+    upm[k] = lanes(get(up, k));
+    parm |= lanes(par);
   }
   uint32_t I, dep = 0;
   V3<uint32_t> c;
   uint4 r;
-  const V3<uint32_t> C0 = deep_coords(q, up, v.R, v.max_depth);
+  const V3<uint32_t> C0 = deep_coords(q, up, v.R, D);
   start_leaf(v, q, up, I, dep, c, r);
-  bool bad = !descend_int(rec, v.n_nodes, C0, v.max_depth, I, dep, c, r);
+  if (!descend_int(rec, v.n_nodes, C0, D, I, dep, c, r)) {
+    out.flags |= CVX_RAYFLAG_BAD_LINK;  // a pool that is not valid
+    return;
+  }
   if (STATS) acc.descent += dep;
+  uint32_t lw = D - dep;
+  V3<uint32_t> E;
+  for (int k = 0; k < 3; ++k)
+    set(E, k, ((get(c, k) << lw) ^ (get(up, k) ? 0u : ~0u)) | ((1u << lw) - 1u));
+  typename LeafLoad<LEAF64>::type pay = LeafLoad<LEAF64>::template load<SMALL>(v.pay, I);
   double T = 1.0;
   V3<double> C{0.0, 0.0, 0.0};
   double t_ent = en.t0;
   uint32_t n_rec = 0;
   uint32_t step = 0;
+  // parameters of the planes after base cell e per axis
+  auto params = [&](const V3<uint32_t>& e) __attribute__((always_inline)) -> V3<double> {
+    return V3<double>{((double)(int32_t)(e.x + 1u) - os.x) * is.x,
+                      ((double)(int32_t)(e.y + 1u) - os.y) * is.y,
+                      ((double)(int32_t)(e.z + 1u) - os.z) * is.z};
+  };
   for (;; ++step) {
-    if (step >= v.max_steps) { out.flags |= CVX_RAYFLAG_STEP_CAP; break; }
-    if (bad) { out.flags |= CVX_RAYFLAG_BAD_LINK; break; }
-    const double h = ldexp(1.0, -(int)dep);
-    double best = __builtin_inf();
-    int kx = 0;
-    for (int k = 0; k < 3; ++k) {
-      const double X = (double)(get(c, k) + (get(up, k) ? 1u : 0u)) * h;
-      const double tt = get(d, k) == 0.0 ? __builtin_inf() : (X - get(o, k)) * get(inv, k);
-      kx = tt < best ? k : kx;
-      best = tt < best ? tt : best;
-    }
-    double len = ldexp(best - t_ent, (int)dep);
-    len = len > 0.0 ? len : 0.0;
-    if (TRACE)
-      for (int k = 0; k < 3; ++k) out.end[k] = get(o, k) + best * get(d, k);
-    double cr, cg, cb, kap;
-    if (v.fmt == CVX_LEAF_F64) {
-      const double4 p = ((const double4*)v.pay)[I];
-      cr = p.x; cg = p.y; cb = p.z; kap = p.w;
-    } else {
-      const uint2 p = ((const uint2*)v.pay)[I];
-      cr = (double)(p.x & 0xffu) / 255.0;
-      cg = (double)((p.x >> 8) & 0xffu) / 255.0;
-      cb = (double)((p.x >> 16) & 0xffu) / 255.0;
-      kap = (double)kappa_of(p);
-    }
-    const double Tn = T * exp(-kap * len);
-    const double a = T - Tn;
-    C.x = __builtin_fma(a, cr, C.x);
-    C.y = __builtin_fma(a, cg, C.y);
-    C.z = __builtin_fma(a, cb, C.z);
-    T = Tn;
-    if (TRACE) record(sk, n_rec, I, len);
-    ++n_rec;
-    const uint32_t ck = get(c, kx);
-    const bool upk = get(up, kx);
-    const Move mv = neighbour(v, I, r, dep, ck, upk, kx);
-    if (mv.at_edge || mv.N >= v.n_nodes || (use_stop && 1.0 - T >= (double)v.alpha_stop)) {
-      if (!mv.at_edge && mv.N >= v.n_nodes) out.flags |= CVX_RAYFLAG_BAD_LINK;
+    if (step >= v.max_steps) {
+      out.flags |= CVX_RAYFLAG_STEP_CAP;
       break;
     }
-    if (STATS) acc.outer += mv.outer;
-    const double X = (double)(upk ? mv.nc : ck) * h;
-    set(c, kx, mv.nc);
-    I = mv.N;
-    r = ld_rec(rec, I);
+    bool stop = false;
     if (is_leaf(r.x)) {
-      const uint32_t dL = leaf_depth(r.x);
-      const uint32_t m = dL < dep ? dep - dL : 0u;
-      for (int k = 0; k < 3; ++k) set(c, k, get(c, k) >> m);
-      dep -= m;
-    } else {
-      for (int k = 0; k < 3; ++k) set(q, k, k == kx ? X : get(o, k) + best * get(d, k));
-      const uint32_t d0 = dep;
-      bad = !descend<double>(rec, v.n_nodes, q, up, I, dep, c, r);
-      if (STATS) acc.descent += dep - d0;
+      const V3<double> t = params(E);
+      const double best = __builtin_fmin(t.x, __builtin_fmin(t.y, t.z));
+      const uint64_t bx = lanes(t.x == best), by = lanes(t.y == best) & ~bx;
+      const bool mx = lane(bx), my = lane(by);
+      const uint32_t Ex = mx ? E.x : (my ? E.y : E.z);
+      bool inner = __builtin_amdgcn_ubfe(Ex, lw, 1u) == 0u;
+      uint32_t Nn = mx ? r.y : (my ? r.z : r.w);
+      Nn = inner ? I ^ (mx ? 1u : (my ? 2u : 4u)) : Nn;
+      if (lw == D) {
+        asm volatile("");  // root array (rare): a branch, not selects
+        inner = false;
+        const bool upk = mx ? up.x : (my ? up.y : up.z);
+        const uint32_t cn = (uint32_t)((int32_t)Ex >> lw) + 1u;
+        const uint32_t ncr = upk ? cn : ~cn;  // true index; wraps to ~0 below 0
+        const uint32_t rs = mx ? 1u : (my ? v.R : v.R * v.R);
+        Nn = ncr >= v.R ? CVX_NONE : (upk ? I + rs : I - rs);
+      }
+      const uint32_t In = Nn < v.n_nodes ? Nn : 0u;
+      const uint4 rn = ld_rec_t<SMALL>(rec, In);
+      double len = ldexp(best - t_ent, (int)(D - lw));
+      len = len > 0.0 ? len : 0.0;
+      if (TRACE)
+        for (int k = 0; k < 3; ++k) out.end[k] = v.o[k] + best * get(d, k);
+      double cr, cg, cb, kap;
+      LeafLoad<LEAF64>::decode(pay, cr, cg, cb, kap);
+      const double Tn = T * exp(-kap * len);
+      const double a = T - Tn;
+      C.x = __builtin_fma(a, cr, C.x);
+      C.y = __builtin_fma(a, cg, C.y);
+      C.z = __builtin_fma(a, cb, C.z);
+      T = Tn;
+      if (TRACE) record(sk, n_rec, I, len);
+      if (TRACE || STATS) ++n_rec;
+      __builtin_amdgcn_sched_barrier(0);
+      stop = (Nn >= v.n_nodes) | (use_stop & (1.0 - T >= (double)v.alpha_stop));
+      if (stop && Nn >= v.n_nodes) {
+        // a null link is the canvas boundary when the exit plane is
+        const bool upk = mx ? up.x : (my ? up.y : up.z);
+        if (Ex + 1u != (upk ? v.R << D : 0u)) out.flags |= CVX_RAYFLAG_BAD_LINK;
+      }
+      if (STATS) acc.outer += !inner && !stop;
+      I = In;
+      r = rn;
+      pay = LeafLoad<LEAF64>::template load<SMALL>(v.pay, I);
+      t_ent = best > t_ent ? best : t_ent;
+      lw = is_leaf(rn.x) ? (D | CVX_XLEAF) - rn.x : lw;
+      const uint32_t low = __builtin_amdgcn_ubfe(~0u, 0u, lw);
+      E.x = plus(E.x, bx) | low;
+      E.y = plus(E.y, by) | low;
+      E.z = plus(E.z, ~(bx | by)) | low;
     }
-    t_ent = best > t_ent ? best : t_ent;
+    if (!is_leaf(r.x) && !stop) {
+      const uint32_t half = 1u << (lw - 1u);
+      const V3<uint32_t> Em{E.x - half, E.y - half, E.z - half};
+      const V3<double> t = params(Em);
+      uint64_t far[3] = {lanes(t.x <= t_ent), lanes(t.y <= t_ent), lanes(t.z <= t_ent)};
+      if (parm) {
+        // along a parallel axis the eye's own base cell tells the side
+        const V3<double> o{v.o[0], v.o[1], v.o[2]};
+        const V3<uint32_t> n = flip(deep_coords(o, up, v.R, D), up);
+        for (int k = 0; k < 3; ++k) {
+          const uint64_t pk = lanes(get(d, k) == 0.0);
+          far[k] = (far[k] & ~pk) | (lanes((int32_t)get(n, k) > (int32_t)get(Em, k)) & pk);
+        }
+      }
+      const uint32_t oct =
+          twice_plus(twice_plus(lane(~(far[2] ^ upm[2])) ? 1u : 0u, ~(far[1] ^ upm[1])),
+                     ~(far[0] ^ upm[0]));
+      E.x = lane(far[0]) ? E.x : Em.x;
+      E.y = lane(far[1]) ? E.y : Em.y;
+      E.z = lane(far[2]) ? E.z : Em.z;
+      lw -= 1u;
+      // (inside the pool for every validated pool; clamped, so that no other
+      // one reads past it)
+      I = __builtin_elementwise_min(r.x + oct, v.n_nodes - 1u);
+      r = ld_rec_t<SMALL>(rec, I);
+      pay = LeafLoad<LEAF64>::template load<SMALL>(v.pay, I);
+      r.x = opaque(r.x);  // waits for the record here, not at the top of the loop
+      if (STATS) acc.descent++;
+    }
+    if (stop) break;
   }
-  out.rgba[0] = C.x;
-  out.rgba[1] = C.y;
-  out.rgba[2] = C.z;
+  const double scale = LeafLoad<LEAF64>::kScale;
+  out.rgba[0] = C.x / scale;
+  out.rgba[1] = C.y / scale;
+  out.rgba[2] = C.z / scale;
   out.rgba[3] = 1.0 - T;
   out.n = n_rec;
   out.steps = step + 1;
@@ -1323,7 +1431,10 @@ __device__ void cast_ray(const DView& v, uint32_t px, uint32_t py, Sink sk, Acc&
   } else if constexpr (VAR == (int)CVX_VARIANT_FP32_REBASED) {
     cast_fp32<TRACE, STATS, SMALL>(v, slot, o, d, inv, en, up, sk, acc, out);
   } else if constexpr (VAR == (int)CVX_VARIANT_FP64_PLAIN) {
-    cast_fp64<TRACE, STATS>(v, d, inv, en, up, sk, acc, out);
+    if (v.fmt == CVX_LEAF_F64)
+      cast_fp64<TRACE, STATS, SMALL, true>(v, d, inv, en, up, sk, acc, out);
+    else
+      cast_fp64<TRACE, STATS, SMALL, false>(v, d, inv, en, up, sk, acc, out);
   } else if constexpr (VAR == (int)CVX_VARIANT_FP32_NAIVE) {
     cast_naive<TRACE, STATS>(v, d, en, up, sk, acc, out);
   } else if constexpr (VAR == (int)CVX_VARIANT_FP32_CELL_LOCAL) {
@@ -1367,7 +1478,8 @@ __device__ __forceinline__ DView uniform_view(const DView& v) {
 // The work items of one wavefront of a persistent grid.  The items are split
 // into contiguous ranges, one per XCD (or one over all), and workgroup b starts
 // on range b mod n_queues.  A wavefront's first item is fixed by its place in
-// the grid; the others are taken from the range's counter, which counts the
+// the grid (in the workgroups that are resident together: one that waits for
+// another to end must not hold an item); the others are taken from the range's counter, which counts the
 // items past the fixed ones, and from the other ranges' once it is exhausted.
 // So a launch with no more items than wavefronts touches no counter, and the
 // first wavefront that finds a range exhausted says so in hdr->drained: the
@@ -1379,12 +1491,15 @@ __device__ __forceinline__ DView uniform_view(const DView& v) {
 // stereo with early stops 534 / 465, depth-24 1920x1080 stereo 959 / 936.
 struct WorkQueue {
   CastHeader* hdr;
+  uint32_t fixed_wgs;  // workgroups with fixed items
   // bits 0-7: ranges known to be exhausted; from bit 8: the current range;
-  // bit 31: the fixed item is taken (opaque: the compiler would peel the loop
+  // bit 31: no fixed item, or it is taken (opaque: the compiler would peel the loop
   // over the items for the first one)
   uint32_t state;
-  __device__ __forceinline__ explicit WorkQueue(CastHeader* h) : hdr(h) {
-    state = (blockIdx.x & (h->n_queues - 1u)) << 8;
+  __device__ __forceinline__ explicit WorkQueue(const CastArgs& a)
+      : hdr(a.hdr), fixed_wgs(a.fixed_wgs) {
+    state = ((blockIdx.x & (hdr->n_queues - 1u)) << 8) |
+            (blockIdx.x < fixed_wgs ? 0u : 1u << 31);
   }
   // The next item into w; false when no range has any left.  Every lane is
   // active here, and all of it is wavefront-uniform.
@@ -1402,7 +1517,7 @@ struct WorkQueue {
       const uint32_t size = (uint32_t)((total * (qi + 1u)) >> log) - first;
       if (!fixed) {
         // the fixed items of range qi: the wavefronts that start on it
-        const uint32_t pre = ((gridDim.x + nq - 1u - qi) >> log) * waves;
+        const uint32_t pre = ((fixed_wgs + nq - 1u - qi) >> log) * waves;
         idx = size;
         if (!((dead >> qi) & 1u) && pre < size) {
           uint32_t taken = 0;
@@ -1437,7 +1552,7 @@ __device__ __forceinline__ void cast_grid(const CastArgs& a) {
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t nv = a.hdr->n_views;
   Acc acc = {0, 0, 0, 0, 0, 0, 0, 0};
-  WorkQueue work(a.hdr);
+  WorkQueue work(a);
   for (uint32_t w = 0; work.next(w);) {
     Out res;
     res.steps = 0;
@@ -1543,7 +1658,7 @@ template <bool SMALL>
 __device__ __forceinline__ void cast_grid_refill(const CastArgs& a) {
   const uint32_t nv = a.hdr->n_views;
   const RaySlot slot{(lds_f64*)(s_ray + threadIdx.x), blockDim.x};
-  WorkQueue work(a.hdr);
+  WorkQueue work(a);
   for (uint32_t w = 0; work.next(w);) {
     int lo = 0, hi = (int)nv - 1;
     while (lo < hi) {
@@ -1625,12 +1740,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CVX_CAST32R
   cast_grid_refill<SMALL>(a);
 }
 
-// The FP64 caster keeps its direction, reciprocal and eye in registers (they
-// enter every step); seven wavefronts per SIMD fit without spills.
-template <bool TRACE, bool STATS, bool OUT64>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void k_cast64(
+// The FP64 caster keeps its scaled eye and reciprocal direction in registers
+// (they enter every step).
+template <bool OUT64, bool SMALL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CVX_CAST64_WAVES))) void k_cast64(
     CastArgs a) {
-  cast_grid<(int)CVX_VARIANT_FP64_PLAIN, TRACE, STATS, OUT64>(a);
+  cast_grid<(int)CVX_VARIANT_FP64_PLAIN, false, false, OUT64, SMALL>(a);
 }
 
 // The leaf holding the eye of view v, into dst (v's place in the device
@@ -1704,10 +1819,14 @@ __global__ __launch_bounds__(256) void k_stage_views(StageViews s, DView* views,
 template <int VAR, bool TRACE, bool STATS, bool OUT64>
 int launch_t(void* stream, const CastArgs& a, uint32_t wgs, uint32_t wg_size) {
   const size_t lds = VAR == (int)CVX_VARIANT_FP32_REBASED ? 9u * sizeof(double) * wg_size : 0u;
-  if constexpr (VAR == (int)CVX_VARIANT_FP64_PLAIN && !TRACE && !STATS)
-    hipLaunchKernelGGL((k_cast64<TRACE, STATS, OUT64>), dim3(wgs), dim3(wg_size), lds,
-                       (hipStream_t)stream, a);
-  else if constexpr (VAR == (int)CVX_VARIANT_FP32_REBASED && TRACE && !STATS && !OUT64) {
+  if constexpr (VAR == (int)CVX_VARIANT_FP64_PLAIN && !TRACE && !STATS) {
+    if (a.small_pools)
+      hipLaunchKernelGGL((k_cast64<OUT64, true>), dim3(wgs), dim3(wg_size), lds,
+                         (hipStream_t)stream, a);
+    else
+      hipLaunchKernelGGL((k_cast64<OUT64, false>), dim3(wgs), dim3(wg_size), lds,
+                         (hipStream_t)stream, a);
+  } else if constexpr (VAR == (int)CVX_VARIANT_FP32_REBASED && TRACE && !STATS && !OUT64) {
     if (a.pieces > 1u)
       hipLaunchKernelGGL((k_cast<VAR, true, false, false, true>), dim3(wgs), dim3(wg_size), lds,
                          (hipStream_t)stream, a);

@@ -191,6 +191,7 @@ struct CastArgs {
   double* end_point;
   uint64_t* stats;
   uint32_t tile_w, tile_h;
+  uint32_t fixed_wgs;    // the first workgroups of the grid, whose wavefronts have a fixed item
   uint32_t small_pools;  // every pool the views read has at most 2^28 nodes
   // FP32 render with lane refill when item_tiles > 1: a work item is up to
   // item_tiles tiles of one view, and waiting lanes take its next rays once
