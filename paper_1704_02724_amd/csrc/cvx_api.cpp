@@ -5,7 +5,6 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <map>
 #include <new>
 #include <string>
 #include <unordered_map>
@@ -56,6 +55,10 @@ struct cvx_ctx {
   // chord pieces of split renders: (colour, T) per pixel and piece
   void* d_split = nullptr;
   size_t split_cap = 0;
+  // the two frontier lists of the link rebuilds, kept from one edit to the next
+  // (grown when a rebuild overflows them, to at most the refined nodes)
+  void* d_links = nullptr;
+  uint64_t links_cap = 0;
   // cvx_render_noalloc: the library's device scratch array on this device
   // (a CastHeader, then the view table) and a pinned host copy of it
   void* d_scratch = nullptr;
@@ -199,6 +202,7 @@ void cvx_destroy(cvx_ctx* ctx) {
   for (auto& c : ctx->canvases) free_canvas(c);
   if (ctx->d_stage) (void)hipFree(ctx->d_stage);
   if (ctx->d_split) (void)hipFree(ctx->d_split);
+  if (ctx->d_links) (void)hipFree(ctx->d_links);
   if (ctx->h_stage) (void)hipHostFree(ctx->h_stage);
   if (ctx->staged) (void)hipEventDestroy(ctx->staged);
   if (ctx->h_scratch) (void)hipHostFree(ctx->h_scratch);
@@ -801,6 +805,10 @@ struct DevBuf {
   }
 };
 
+// Counts of a link rebuild: the region roots, then one per level and the next.
+constexpr uint32_t kLinkCounts = 1 + CVX_MAX_DEPTH + 2;
+constexpr uint64_t kLinkListMin = 1u << 18;  // nodes a frontier list starts with
+
 // The edits of cvx_edit_pool on a present canvas (also the splits of a
 // stroke step).
 int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edits,
@@ -904,6 +912,9 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
     }
   }
 
+  if (paint.size() > 0xffffff00ull)
+    return rollback(CVX_ERR_OOM, "more payloads in one batch than the marks can number");
+
   // ---- device: grow, scatter records and payloads, rebuild G_3 and the table
   auto device_fail = [&](hipError_t e, const char* where) {
     // the device may be partly updated: mark the mirror stale so the next
@@ -949,39 +960,51 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
   }
   c.n_nodes = n_cur;
 
-  // last record word and last payload per node
-  std::sort(touched.begin(), touched.end());
-  touched.erase(std::unique(touched.begin(), touched.end()), touched.end());
-  std::vector<uint32_t> xs(touched.size());
-  for (size_t j = 0; j < touched.size(); ++j) xs[j] = c.mirror[touched[j]];
-  std::vector<std::pair<uint32_t, uint64_t>> last;
-  {
-    std::vector<std::pair<uint32_t, uint64_t>> tmp;
-    tmp.reserve(paint.size());
-    for (size_t j = 0; j < paint.size(); ++j) tmp.emplace_back(paint[j].first, j);
-    std::stable_sort(tmp.begin(), tmp.end(),
-                     [](const auto& a, const auto& b) { return a.first < b.first; });
-    for (size_t j = 0; j < tmp.size(); ++j)
-      if (j + 1 == tmp.size() || tmp[j + 1].first != tmp[j].first)
-        last.emplace_back(tmp[j].first, paint[tmp[j].second].second);
-  }
-  std::vector<uint32_t> pay_ids(last.size());
-  std::vector<uint8_t> pay_src(last.size() * lb);
-  for (size_t j = 0; j < last.size(); ++j) {
-    pay_ids[j] = last[j].first;
-    std::memcpy(pay_src.data() + j * lb, (const uint8_t*)payloads + last[j].second * lb, lb);
-  }
+  // the batch as one block: record words (a node listed twice has its final
+  // word in both places), payloads in the order of the edits, changed nodes
   const uint32_t R = c.desc.R;
   uint32_t depth = 0;
   for (uint32_t d = 0; d < 64; ++d)
     if (c.leaves_at_depth[d]) depth = d;
-  std::vector<uint32_t> ch_ids, ch_depth;
-  for (const auto& kv : changed) {
-    ch_ids.push_back(kv.first);
-    ch_depth.push_back(kv.second);
+  const uint64_t n_touched = touched.size(), n_paint = paint.size(), n_changed = changed.size();
+  uint64_t at = 0;
+  auto section = [&](uint64_t bytes) {
+    const uint64_t o = at;
+    at += (bytes + 15) & ~15ull;
+    return o;
+  };
+  const uint64_t o_ids = section(4 * n_touched), o_xs = section(4 * n_touched);
+  const uint64_t o_pids = section(4 * n_paint), o_psrc = section(lb * n_paint);
+  const uint64_t o_ch = section(4 * n_changed), o_chd = section(4 * n_changed);
+  const uint64_t o_counts = section(4 * kLinkCounts);  // [0]: region roots; then per level
+  const uint64_t up_bytes = at;                        // the rest is written on the device
+  const uint64_t o_roots = section(4 * 7 * n_changed), o_rootd = section(4 * 7 * n_changed);
+  std::vector<uint8_t> blob(up_bytes, 0);
+  uint32_t d_first = 64;
+  {
+    uint32_t* ids = (uint32_t*)(blob.data() + o_ids);
+    uint32_t* xs = (uint32_t*)(blob.data() + o_xs);
+    for (uint64_t j = 0; j < n_touched; ++j) {
+      ids[j] = touched[j];
+      xs[j] = c.mirror[touched[j]];
+    }
+    uint32_t* pids = (uint32_t*)(blob.data() + o_pids);
+    for (uint64_t j = 0; j < n_paint; ++j) {
+      pids[j] = paint[j].first;
+      std::memcpy(blob.data() + o_psrc + j * lb, (const uint8_t*)payloads + paint[j].second * lb,
+                  lb);
+    }
+    uint32_t* ch = (uint32_t*)(blob.data() + o_ch);
+    uint32_t* chd = (uint32_t*)(blob.data() + o_chd);
+    uint64_t j = 0;
+    for (const auto& kv : changed) {
+      ch[j] = kv.first;
+      chd[j++] = kv.second;
+      d_first = std::min(d_first, kv.second);
+    }
   }
 
-  DevBuf b_ids, b_xs, b_pids, b_psrc, b_order, b_count, b_ch, b_chd, b_roots, b_rootd;
+  DevBuf b_blob;
   hipError_t e = hipSuccess;
   const char* where = "";
 #define STEP(call)                      \
@@ -989,109 +1012,84 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
     e = (call);                         \
     if (e != hipSuccess) where = #call; \
   }
-  const uint64_t n_changed = ch_ids.size();
-  STEP(hipMalloc(&b_ids.p, std::max<size_t>(touched.size(), 1) * 4));
-  STEP(hipMalloc(&b_xs.p, std::max<size_t>(touched.size(), 1) * 4));
-  STEP(hipMalloc(&b_pids.p, std::max<size_t>(pay_ids.size(), 1) * 4));
-  STEP(hipMalloc(&b_psrc.p, std::max<size_t>(pay_src.size(), 8)));
-  STEP(hipMalloc(&b_ch.p, std::max<uint64_t>(n_changed, 1) * 4));
-  STEP(hipMalloc(&b_chd.p, std::max<uint64_t>(n_changed, 1) * 4));
-  STEP(hipMalloc(&b_roots.p, std::max<uint64_t>(7 * n_changed, 1) * 4));
-  STEP(hipMalloc(&b_rootd.p, std::max<uint64_t>(7 * n_changed, 1) * 4));
-  STEP(hipMalloc(&b_count.p, 4));
+#define LAUNCH(call, name)              \
+  if (e == hipSuccess) {                \
+    e = (hipError_t)(call);             \
+    if (e != hipSuccess) where = name;  \
+  }
+  STEP(hipMalloc(&b_blob.p, std::max<uint64_t>(at, 16)));
   if (e == hipSuccess && c.mark_cap < c.n_nodes) {
-    // per-node visit marks of the link rebuild (epochs), grown with the pool
+    // marks, grown with the pool
     if (c.mark) (void)hipFree(c.mark);
     c.mark = nullptr;
     c.mark_cap = 0;
     STEP(hipMalloc((void**)&c.mark, c.cap_nodes * 4));
     STEP(hipMemsetAsync(c.mark, 0, c.cap_nodes * 4, ctx->stream));
     if (e == hipSuccess) c.mark_cap = c.cap_nodes;
+  } else if (e == hipSuccess && c.epoch > 0xffffffffu - n_paint - 64u) {
+    // the running count starts again
+    STEP(hipMemsetAsync(c.mark, 0, c.mark_cap * 4, ctx->stream));
+    c.epoch = 0;
   }
   if (e != hipSuccess) return device_fail(e, where);
-  if (!touched.empty()) {
-    STEP(hipMemcpyAsync(b_ids.p, touched.data(), touched.size() * 4, hipMemcpyHostToDevice, ctx->stream));
-    STEP(hipMemcpyAsync(b_xs.p, xs.data(), xs.size() * 4, hipMemcpyHostToDevice, ctx->stream));
-    if (e == hipSuccess) {
-      int le = cvx::launch_scatter_records(ctx->stream, (const uint32_t*)b_ids.p,
-                                           (const uint32_t*)b_xs.p, touched.size(), c.rec);
-      if (le != hipSuccess) { e = (hipError_t)le; where = "k_scatter_records"; }
-    }
-  }
-  if (!pay_ids.empty()) {
-    STEP(hipMemcpyAsync(b_pids.p, pay_ids.data(), pay_ids.size() * 4, hipMemcpyHostToDevice, ctx->stream));
-    STEP(hipMemcpyAsync(b_psrc.p, pay_src.data(), pay_src.size(), hipMemcpyHostToDevice, ctx->stream));
-    if (e == hipSuccess) {
-      int le = cvx::launch_scatter_payloads(ctx->stream, (const uint32_t*)b_pids.p, b_psrc.p,
-                                            pay_ids.size(), lb, c.pay);
-      if (le != hipSuccess) { e = (hipError_t)le; where = "k_scatter_payloads"; }
-    }
-  }
+  uint8_t* blk = (uint8_t*)b_blob.p;
+  STEP(hipMemcpyAsync(blk, blob.data(), up_bytes, hipMemcpyHostToDevice, ctx->stream));
+  LAUNCH(cvx::launch_scatter_records(ctx->stream, (const uint32_t*)(blk + o_ids),
+                                     (const uint32_t*)(blk + o_xs), n_touched, c.rec),
+         "k_scatter_records");
+  LAUNCH(cvx::launch_scatter_payloads(ctx->stream, (const uint32_t*)(blk + o_pids), blk + o_psrc,
+                                      n_paint, lb, c.pay, c.mark, c.epoch + 1u),
+         "k_scatter_payloads");
+  c.epoch += (uint32_t)n_paint;
   // G_3 below the changed regions (Sec. 4.1.2), on the final records: the
   // roots of the regions come from the device, then the links are derived
   // level by level as at upload, each level's frontier being the refined
   // children reached from the level above plus the region roots of that depth
-  std::map<uint32_t, std::vector<uint32_t>> roots_at;
-  uint64_t n_roots = 0;
   if (n_changed) {
-    const uint32_t zero = 0;
-    STEP(hipMemcpyAsync(b_ch.p, ch_ids.data(), n_changed * 4, hipMemcpyHostToDevice, ctx->stream));
-    STEP(hipMemcpyAsync(b_chd.p, ch_depth.data(), n_changed * 4, hipMemcpyHostToDevice, ctx->stream));
-    STEP(hipMemcpyAsync(b_count.p, &zero, 4, hipMemcpyHostToDevice, ctx->stream));
-    if (e == hipSuccess) {
-      int le = cvx::launch_dirty_roots(ctx->stream, (const uint32_t*)b_ch.p, (const uint32_t*)b_chd.p,
-                                       n_changed, c.rec, R, (uint32_t*)b_roots.p,
-                                       (uint32_t*)b_rootd.p, (uint32_t*)b_count.p, c.n_nodes);
-      if (le != hipSuccess) { e = (hipError_t)le; where = "k_dirty_roots"; }
-    }
-    uint32_t cnt = 0;
-    STEP(hipMemcpyAsync(&cnt, b_count.p, 4, hipMemcpyDeviceToHost, ctx->stream));
-    STEP(hipStreamSynchronize(ctx->stream));
-    if (e == hipSuccess && cnt > 7 * n_changed) { e = hipErrorUnknown; where = "region roots overflow"; }
-    std::vector<uint32_t> rid(cnt), rd(cnt);
-    if (cnt) {
-      STEP(hipMemcpy(rid.data(), b_roots.p, cnt * 4, hipMemcpyDeviceToHost));
-      STEP(hipMemcpy(rd.data(), b_rootd.p, cnt * 4, hipMemcpyDeviceToHost));
-    }
-    for (uint32_t j = 0; e == hipSuccess && j < cnt; ++j) roots_at[rd[j]].push_back(rid[j]);
-    for (auto& kv : roots_at) {
-      std::sort(kv.second.begin(), kv.second.end());
-      kv.second.erase(std::unique(kv.second.begin(), kv.second.end()), kv.second.end());
-      n_roots += kv.second.size();
-    }
-  }
-  if (e == hipSuccess && !roots_at.empty()) {
-    const uint64_t cap = c.n_refined + n_roots;
-    STEP(hipMalloc(&b_order.p, std::max<uint64_t>(cap, 1) * 4));
-    const uint32_t epoch = ++c.epoch;  // marks hold 0 or an earlier epoch
-    uint64_t lo = 0, hi = 0;
-    auto it = roots_at.begin();
-    for (uint32_t level = it->first; e == hipSuccess; ++level) {
-      if (it != roots_at.end() && it->first == level) {
-        if (hi + it->second.size() > cap) { e = hipErrorUnknown; where = "link frontier overflow"; break; }
-        STEP(hipMemcpyAsync((uint32_t*)b_order.p + hi, it->second.data(), it->second.size() * 4,
-                            hipMemcpyHostToDevice, ctx->stream));
-        hi += it->second.size();
-        ++it;
+    uint32_t* counts = (uint32_t*)(blk + o_counts);
+    LAUNCH(cvx::launch_dirty_roots(ctx->stream, (const uint32_t*)(blk + o_ch),
+                                   (const uint32_t*)(blk + o_chd), n_changed, c.rec, R,
+                                   (uint32_t*)(blk + o_roots), (uint32_t*)(blk + o_rootd), counts,
+                                   c.n_nodes),
+           "k_dirty_roots");
+    // no frontier is larger than the refined nodes; most are far smaller, so
+    // the lists start small and a rebuild that overflows them runs again
+    const uint64_t most = c.n_refined + 1;
+    for (bool again = true; e == hipSuccess && again && depth > d_first;) {
+      again = false;
+      if (ctx->links_cap < std::min<uint64_t>(most, kLinkListMin)) {
+        if (ctx->d_links) (void)hipFree(ctx->d_links);
+        ctx->d_links = nullptr;
+        ctx->links_cap = 0;
+        STEP(hipMalloc(&ctx->d_links, 2 * kLinkListMin * 4));
+        if (e == hipSuccess) ctx->links_cap = kLinkListMin;
       }
-      if (hi == lo) {
-        if (it == roots_at.end()) break;
-        continue;
-      }
-      const uint32_t h32 = (uint32_t)hi;
-      STEP(hipMemcpyAsync(b_count.p, &h32, 4, hipMemcpyHostToDevice, ctx->stream));
-      if (e != hipSuccess) break;
-      int le = cvx::launch_links_level(ctx->stream, (const uint32_t*)b_order.p + lo, hi - lo, level,
-                                       c.rec, R, (uint32_t*)b_order.p, (uint32_t*)b_count.p,
-                                       c.n_nodes, c.mark, epoch);
-      if (le != hipSuccess) { e = (hipError_t)le; where = "k_links_level"; break; }
-      uint32_t cnt = 0;
-      STEP(hipMemcpyAsync(&cnt, b_count.p, 4, hipMemcpyDeviceToHost, ctx->stream));
+      LAUNCH(cvx::launch_links(ctx->stream, d_first, depth - 1, c.rec, R,
+                               (const uint32_t*)(blk + o_roots), (const uint32_t*)(blk + o_rootd),
+                               counts, (uint32_t*)ctx->d_links, (uint32_t)ctx->links_cap,
+                               counts + 1, c.n_nodes, c.mark, ++c.epoch),
+             "k_links_level");
+      uint32_t got[kLinkCounts] = {0};
+      STEP(hipMemcpyAsync(got, counts, sizeof(got), hipMemcpyDeviceToHost, ctx->stream));
       STEP(hipStreamSynchronize(ctx->stream));
       if (e != hipSuccess) break;
-      if (cnt > cap) { e = hipErrorUnknown; where = "link frontier overflow"; break; }
-      lo = hi;
-      hi = cnt;
+      uint32_t large = 0;
+      for (uint32_t l = 1; l < kLinkCounts; ++l) large = std::max(large, got[l]);
+      if (got[0] > 7 * n_changed || large > most) {
+        e = hipErrorUnknown;
+        where = "link frontier overflow";
+      } else if (large > ctx->links_cap) {
+        again = true;
+        (void)hipFree(ctx->d_links);
+        ctx->d_links = nullptr;
+        const uint64_t cap = std::min<uint64_t>(most, 2 * (uint64_t)large);
+        ctx->links_cap = 0;
+        STEP(hipMalloc(&ctx->d_links, 2 * cap * 4));
+        if (e == hipSuccess) ctx->links_cap = cap;
+        for (uint32_t l = 1; l < kLinkCounts; ++l) got[l] = 0;
+        STEP(hipMemcpyAsync(counts, got, sizeof(got), hipMemcpyHostToDevice, ctx->stream));
+        STEP(hipStreamSynchronize(ctx->stream));
+      }
     }
   }
   // top-level table for the new depth
@@ -1112,6 +1110,7 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
   }
   STEP(hipStreamSynchronize(ctx->stream));
 #undef STEP
+#undef LAUNCH
   if (e != hipSuccess) return device_fail(e, where);
   c.depth = depth;
   return CVX_OK;

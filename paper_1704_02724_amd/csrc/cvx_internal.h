@@ -100,7 +100,9 @@ struct DevCanvas {
   std::vector<uint32_t> free_groups;
   std::vector<uint64_t> leaves_at_depth;
   uint64_t n_refined = 0;  // refined nodes in the tree
-  uint32_t* mark = nullptr;  // per node: last edit call whose link rebuild visited it
+  // per node: the position of its last paint or the number of the link rebuild
+  // that last visited it, both from the running count `epoch`
+  uint32_t* mark = nullptr;
   uint64_t mark_cap = 0;
   uint32_t epoch = 0;
   StrokeState stroke;
@@ -213,10 +215,14 @@ int launch_extract_x(void* stream, const void* rec, uint64_t n, uint32_t* out);
 int launch_scatter_records(void* stream, const uint32_t* ids, const uint32_t* xs, uint64_t n,
                            void* rec);
 int launch_scatter_payloads(void* stream, const uint32_t* ids, const void* src, uint64_t n,
-                            uint32_t leaf_bytes, void* pay);
-int launch_links_level(void* stream, const uint32_t* frontier, uint64_t n, uint32_t level,
-                       void* rec, uint32_t R, uint32_t* next, uint32_t* next_count,
-                       uint64_t n_nodes, uint32_t* mark, uint32_t epoch);
+                            uint32_t leaf_bytes, void* pay, uint32_t* mark, uint32_t base);
+// the outer links below the region roots, level by level: frontiers holds two
+// lists of cap nodes, counts one count per level (zeroed by the caller, the
+// counts of levels first_level + 1 .. last_level + 1 are left in it)
+int launch_links(void* stream, uint32_t first_level, uint32_t last_level, void* rec, uint32_t R,
+                 const uint32_t* roots, const uint32_t* root_depth, const uint32_t* n_roots,
+                 uint32_t* frontiers, uint32_t cap, uint32_t* counts, uint64_t n_nodes,
+                 uint32_t* mark, uint32_t epoch);
 int launch_dirty_roots(void* stream, const uint32_t* changed, const uint32_t* depth, uint64_t n,
                        const void* rec, uint32_t R, uint32_t* out, uint32_t* out_depth,
                        uint32_t* out_count, uint64_t n_nodes);
