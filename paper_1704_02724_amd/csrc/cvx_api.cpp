@@ -59,6 +59,8 @@ struct cvx_ctx {
   // (grown when a rebuild overflows them, to at most the refined nodes)
   void* d_links = nullptr;
   uint64_t links_cap = 0;
+  // blocks of the strokes' walks, kept from one to the next
+  void* d_walk[2] = {nullptr, nullptr};
   // cvx_render_noalloc: the library's device scratch array on this device
   // (a CastHeader, then the view table) and a pinned host copy of it
   void* d_scratch = nullptr;
@@ -203,6 +205,8 @@ void cvx_destroy(cvx_ctx* ctx) {
   if (ctx->d_stage) (void)hipFree(ctx->d_stage);
   if (ctx->d_split) (void)hipFree(ctx->d_split);
   if (ctx->d_links) (void)hipFree(ctx->d_links);
+  for (void* p : ctx->d_walk)
+    if (p) (void)hipFree(p);
   if (ctx->h_stage) (void)hipHostFree(ctx->h_stage);
   if (ctx->staged) (void)hipEventDestroy(ctx->staged);
   if (ctx->h_scratch) (void)hipHostFree(ctx->h_scratch);
@@ -1041,10 +1045,27 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
                                       n_paint, lb, c.pay, c.mark, c.epoch + 1u),
          "k_scatter_payloads");
   c.epoch += (uint32_t)n_paint;
+  // top-level table for the new depth (record words only)
+  const uint32_t L = cvx::top_table_depth(R, depth);
+  if (e == hipSuccess && L != c.top_depth) {
+    if (c.top) (void)hipFree(c.top);
+    c.top = nullptr;
+    c.top_depth = 0;
+    if (L) {
+      const uint64_t side = (uint64_t)R << L;
+      STEP(hipMalloc((void**)&c.top, side * side * side * 4));
+      if (e == hipSuccess) c.top_depth = L;
+    }
+  }
+  if (e == hipSuccess && c.top_depth) {
+    int le = cvx::launch_top_table(ctx->stream, c.rec, c.n_nodes, R, c.top_depth, c.top);
+    if (le != hipSuccess) { e = (hipError_t)le; where = "k_top_table"; }
+  }
   // G_3 below the changed regions (Sec. 4.1.2), on the final records: the
   // roots of the regions come from the device, then the links are derived
   // level by level as at upload, each level's frontier being the refined
   // children reached from the level above plus the region roots of that depth
+  bool synced = false;
   if (n_changed) {
     uint32_t* counts = (uint32_t*)(blk + o_counts);
     LAUNCH(cvx::launch_dirty_roots(ctx->stream, (const uint32_t*)(blk + o_ch),
@@ -1073,6 +1094,7 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
       STEP(hipMemcpyAsync(got, counts, sizeof(got), hipMemcpyDeviceToHost, ctx->stream));
       STEP(hipStreamSynchronize(ctx->stream));
       if (e != hipSuccess) break;
+      synced = true;
       uint32_t large = 0;
       for (uint32_t l = 1; l < kLinkCounts; ++l) large = std::max(large, got[l]);
       if (got[0] > 7 * n_changed || large > most) {
@@ -1092,23 +1114,7 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
       }
     }
   }
-  // top-level table for the new depth
-  const uint32_t L = cvx::top_table_depth(R, depth);
-  if (e == hipSuccess && L != c.top_depth) {
-    if (c.top) (void)hipFree(c.top);
-    c.top = nullptr;
-    c.top_depth = 0;
-    if (L) {
-      const uint64_t side = (uint64_t)R << L;
-      STEP(hipMalloc((void**)&c.top, side * side * side * 4));
-      if (e == hipSuccess) c.top_depth = L;
-    }
-  }
-  if (e == hipSuccess && c.top_depth) {
-    int le = cvx::launch_top_table(ctx->stream, c.rec, c.n_nodes, R, c.top_depth, c.top);
-    if (le != hipSuccess) { e = (hipError_t)le; where = "k_top_table"; }
-  }
-  STEP(hipStreamSynchronize(ctx->stream));
+  if (!synced) STEP(hipStreamSynchronize(ctx->stream));
 #undef STEP
 #undef LAUNCH
   if (e != hipSuccess) return device_fail(e, where);
@@ -1200,17 +1206,24 @@ void child_payload(const uint8_t* parent, uint32_t fmt, uint8_t* child) {
   child[6] = child[7] = 0;
 }
 
+// Cells of each list of a stroke's walk that a context keeps; a frontier that
+// could outgrow them gets lists of its own.
+constexpr uint64_t kWalkCells = 1u << 16;
+constexpr uint32_t kWalkLevels = 8;       // levels between two read-backs at most
+constexpr uint32_t kWalkHead = 64;        // bytes: pending count, then a count per level
+constexpr uint64_t kWalkFirst = 512;      // pending entries that come with the counts
+
 // One walk of the stroke from a frontier (nullptr: the root array) down to
-// the leaves, level by level on the GPU; the leaves still waiting for a split
-// are appended to c.stroke.pending with their payloads from before the stroke.
+// the leaves on the GPU; the leaves still waiting for a split are appended to
+// c.stroke.pending with their payloads from before the stroke.  A frontier
+// grows at most eightfold a level, so as many levels run without a read-back
+// as surely fit the lists (5 from a single root, then about 3).
 int stroke_walk(cvx_ctx* ctx, DevCanvas& c, const std::vector<cvx::StrokeItem>* start,
                 uint32_t merge = 0) {
   cvx::StrokeState& st = c.stroke;
-  const uint32_t lb = leaf_bytes(c.desc.leaf_format);
   const uint32_t R = c.desc.R;
   uint64_t n = start ? start->size() : (uint64_t)R * R * R;
   if (!n) return CVX_OK;
-  DevBuf b_stamps, b_cur, b_count;
   hipError_t e = hipSuccess;
   const char* where = "";
 #define STEP(call)                      \
@@ -1218,46 +1231,72 @@ int stroke_walk(cvx_ctx* ctx, DevCanvas& c, const std::vector<cvx::StrokeItem>* 
     e = (call);                         \
     if (e != hipSuccess) where = #call; \
   }
-  STEP(hipMalloc(&b_stamps.p, st.stamps.size() * 8));
-  STEP(hipMemcpyAsync(b_stamps.p, st.stamps.data(), st.stamps.size() * 8, hipMemcpyHostToDevice,
-                      ctx->stream));
-  STEP(hipMalloc(&b_count.p, 8));
-  if (start) {
-    STEP(hipMalloc(&b_cur.p, n * sizeof(cvx::StrokeItem)));
-    STEP(hipMemcpyAsync(b_cur.p, start->data(), n * sizeof(cvx::StrokeItem),
-                        hipMemcpyHostToDevice, ctx->stream));
-  }
-  for (uint32_t level = 0; e == hipSuccess && n; ++level) {
+  // stamps and the first frontier, one copy
+  const uint64_t o_start = (st.stamps.size() * 8 + 31) & ~31ull;
+  std::vector<uint8_t> blob(o_start + (start ? n * sizeof(cvx::StrokeItem) : 0));
+  std::memcpy(blob.data(), st.stamps.data(), st.stamps.size() * 8);
+  if (start) std::memcpy(blob.data() + o_start, start->data(), n * sizeof(cvx::StrokeItem));
+  DevBuf b_in, b_own[2];
+  STEP(hipMalloc(&b_in.p, blob.size()));
+  STEP(hipMemcpyAsync(b_in.p, blob.data(), blob.size(), hipMemcpyHostToDevice, ctx->stream));
+  const cvx::StrokeItem* items =
+      start ? (const cvx::StrokeItem*)((uint8_t*)b_in.p + o_start) : nullptr;
+  std::vector<uint8_t> got(kWalkHead + kWalkFirst * sizeof(cvx::StrokePend));
+  for (uint32_t turn = 0; e == hipSuccess && n; ++turn) {
     if (n > 0x1fffffffull) { e = hipErrorUnknown; where = "stroke frontier too large"; break; }
-    DevBuf b_next, b_pend, b_ppay;
-    STEP(hipMalloc(&b_next.p, 8 * n * sizeof(cvx::StrokeItem)));
-    STEP(hipMalloc(&b_pend.p, n * sizeof(cvx::StrokeItem)));
-    STEP(hipMalloc(&b_ppay.p, n * lb));
-    STEP(hipMemsetAsync(b_count.p, 0, 8, ctx->stream));
+    // levels that surely fit; a frontier too large for one gets its own lists
+    uint32_t levels = 0;
+    for (uint64_t m = n * 8; levels < kWalkLevels && m <= kWalkCells; m *= 8) ++levels;
+    uint64_t cap = kWalkCells;
+    if (!levels) {
+      levels = 1;
+      cap = 8 * n;
+    }
+    // a block of [head | pending | two lists]; turns alternate between two, so
+    // that the frontier a turn starts from is not one it writes
+    const uint64_t bytes = kWalkHead + cap * sizeof(cvx::StrokePend) +
+                           2 * cap * sizeof(cvx::StrokeItem);
+    uint8_t* blk = nullptr;
+    if (cap == kWalkCells) {
+      for (int k = 0; k < 2 && e == hipSuccess; ++k)
+        if (!ctx->d_walk[k]) STEP(hipMalloc(&ctx->d_walk[k], bytes));
+      blk = (uint8_t*)ctx->d_walk[turn & 1u];
+    } else {
+      DevBuf& own = b_own[turn & 1u];
+      if (own.p) (void)hipFree(own.p);
+      own.p = nullptr;
+      STEP(hipMalloc(&own.p, bytes));
+      blk = (uint8_t*)own.p;
+    }
     if (e != hipSuccess) break;
-    uint32_t* cnt = (uint32_t*)b_count.p;
-    int le = cvx::launch_stroke_visit(ctx->stream, (const cvx::StrokeItem*)b_cur.p, (uint32_t)n,
-                                      st.args, b_stamps.p, c.rec, c.pay, c.n_nodes,
-                                      (cvx::StrokeItem*)b_next.p, cnt, (uint32_t)(8 * n),
-                                      (cvx::StrokeItem*)b_pend.p, b_ppay.p, cnt + 1, (uint32_t)n,
-                                      merge);
+    uint32_t head[kWalkHead / 4] = {0, (uint32_t)n};
+    cvx::StrokePend* pend = (cvx::StrokePend*)(blk + kWalkHead);
+    cvx::StrokeItem* lists = (cvx::StrokeItem*)(blk + kWalkHead + cap * sizeof(cvx::StrokePend));
+    STEP(hipMemcpyAsync(blk, head, kWalkHead, hipMemcpyHostToDevice, ctx->stream));
+    if (e != hipSuccess) break;
+    uint32_t* counts = (uint32_t*)blk;
+    int le = cvx::launch_stroke_visit(ctx->stream, levels, items, (uint32_t)n, st.args, b_in.p,
+                                      c.rec, c.pay, c.n_nodes, lists, (uint32_t)cap, counts + 1,
+                                      pend, counts, (uint32_t)cap, merge);
     if (le != hipSuccess) { e = (hipError_t)le; where = "k_stroke_visit"; break; }
-    uint32_t h[2] = {0, 0};
-    STEP(hipMemcpyAsync(h, b_count.p, 8, hipMemcpyDeviceToHost, ctx->stream));
+    STEP(hipMemcpyAsync(got.data(), blk, got.size(), hipMemcpyDeviceToHost, ctx->stream));
     STEP(hipStreamSynchronize(ctx->stream));
     if (e != hipSuccess) break;
-    if (h[0] > 8 * n || h[1] > n) { e = hipErrorUnknown; where = "stroke frontier overflow"; break; }
-    if (h[1]) {
-      const size_t p0 = st.pending.size();
-      st.pending.resize(p0 + h[1]);
-      st.pending_pay.resize((p0 + h[1]) * lb);
-      STEP(hipMemcpy(st.pending.data() + p0, b_pend.p, h[1] * sizeof(cvx::StrokeItem),
-                     hipMemcpyDeviceToHost));
-      STEP(hipMemcpy(st.pending_pay.data() + p0 * lb, b_ppay.p, (size_t)h[1] * lb,
-                     hipMemcpyDeviceToHost));
+    uint32_t h[kWalkHead / 4];
+    std::memcpy(h, got.data(), kWalkHead);
+    bool over = h[0] > cap;
+    for (uint32_t l = 0; l < levels; ++l) over = over || h[2 + l] > cap;
+    if (over) { e = hipErrorUnknown; where = "stroke frontier overflow"; break; }
+    if (h[0]) {
+      const size_t p0 = st.pending.size(), with = std::min<size_t>(h[0], kWalkFirst);
+      st.pending.resize(p0 + h[0]);
+      std::memcpy(st.pending.data() + p0, got.data() + kWalkHead, with * sizeof(cvx::StrokePend));
+      if (h[0] > with)
+        STEP(hipMemcpy(st.pending.data() + p0 + with, pend + with,
+                       (h[0] - with) * sizeof(cvx::StrokePend), hipMemcpyDeviceToHost));
     }
-    std::swap(b_cur.p, b_next.p);
-    n = h[0];
+    n = h[1 + levels];
+    items = lists + ((levels - 1u) & 1u) * cap;
   }
 #undef STEP
   if (e != hipSuccess) return hip_fail(ctx, e, where);
@@ -1305,8 +1344,8 @@ int stroke_merge_step(cvx_ctx* ctx, DevCanvas& c) {
   std::vector<uint8_t> pays;
   for (size_t i = 0; i < st.pending.size(); ++i) {
     uint8_t pp[32];
-    if (!parent_payload(st.pending_pay.data() + i * lb, fmt, pp)) continue;
-    nodes.push_back(st.pending[i].node);
+    if (!parent_payload((const uint8_t*)st.pending[i].pay, fmt, pp)) continue;
+    nodes.push_back(st.pending[i].item.node);
     pays.insert(pays.end(), pp, pp + lb);
   }
   std::vector<uint32_t> ord(nodes.size());
@@ -1319,7 +1358,6 @@ int stroke_merge_step(cvx_ctx* ctx, DevCanvas& c) {
     edits[i].first_payload = ord[i];
   }
   st.pending.clear();
-  st.pending_pay.clear();
   if (!edits.empty()) {
     int rc = edit_impl(ctx, c, edits.data(), (uint32_t)edits.size(), pays.data(),
                        (uint64_t)nodes.size(), nullptr);
@@ -1355,15 +1393,17 @@ int stroke_step_impl(cvx_ctx* ctx, DevCanvas& c, uint64_t* pending) {
   std::vector<uint32_t> ord(n);
   for (size_t i = 0; i < n; ++i) ord[i] = (uint32_t)i;
   std::sort(ord.begin(), ord.end(),
-            [&](uint32_t a, uint32_t b) { return st.pending[a].node < st.pending[b].node; });
+            [&](uint32_t a, uint32_t b) {
+              return st.pending[a].item.node < st.pending[b].item.node;
+            });
   std::vector<cvx_edit> edits(n);
   std::vector<uint8_t> pays(n * 8 * lb);
   for (size_t i = 0; i < n; ++i) {
     edits[i].op = CVX_EDIT_REFINE;
-    edits[i].node = st.pending[ord[i]].node;
+    edits[i].node = st.pending[ord[i]].item.node;
     edits[i].first_payload = 8 * (uint64_t)i;
     uint8_t cp[32];
-    child_payload(st.pending_pay.data() + (size_t)ord[i] * lb, fmt, cp);
+    child_payload((const uint8_t*)st.pending[ord[i]].pay, fmt, cp);
     for (uint32_t o = 0; o < 8; ++o) std::memcpy(pays.data() + (8 * i + o) * lb, cp, lb);
   }
   std::vector<uint32_t> first(n);
@@ -1375,7 +1415,7 @@ int stroke_step_impl(cvx_ctx* ctx, DevCanvas& c, uint64_t* pending) {
   }
   std::vector<cvx::StrokeItem> kids(8 * n);
   for (size_t i = 0; i < n; ++i) {
-    const cvx::StrokeItem& p = st.pending[ord[i]];
+    const cvx::StrokeItem& p = st.pending[ord[i]].item;
     for (uint32_t o = 0; o < 8; ++o) {
       cvx::StrokeItem& k = kids[8 * i + o];
       k = cvx::StrokeItem{};
@@ -1387,7 +1427,6 @@ int stroke_step_impl(cvx_ctx* ctx, DevCanvas& c, uint64_t* pending) {
     }
   }
   st.pending.clear();
-  st.pending_pay.clear();
   rc = stroke_walk(ctx, c, &kids);
   if (rc == CVX_OK) rc = stroke_enter_merge(ctx, c);
   if (rc != CVX_OK) {

@@ -59,6 +59,13 @@ struct StrokeItem {
   uint32_t node, x, y, z, depth, pad0, pad1, pad2;
 };
 
+// A leaf waiting for a split, or a cell for a merge: with its payload from
+// before the stroke (RGBA8 leaves: the first word).
+struct StrokePend {
+  StrokeItem item;
+  uint64_t pay[4];
+};
+
 // One stroke in device-ready form (world units, as the canvas descriptor).
 struct StrokeArgs {
   double origin[3];
@@ -77,8 +84,7 @@ struct StrokeState {
   bool merging = false;  // pending holds cells to merge, not leaves to split
   StrokeArgs args{};
   std::vector<double> stamps;  // 4 per stamp: x, y, z, r
-  std::vector<StrokeItem> pending;
-  std::vector<uint8_t> pending_pay;
+  std::vector<StrokePend> pending;
 };
 
 struct DevCanvas {
@@ -247,12 +253,14 @@ int launch_view_starts(void* stream, DView* views, CastHeader* hdr, uint32_t ena
 int launch_stage_views(void* stream, const DView* host_views, uint32_t n_views,
                        const CastHeader& host_hdr, DView* views, CastHeader* hdr,
                        uint32_t enable);
-// one level of a stroke's walk (cvx_stroke.hip); items == nullptr: the roots;
-// merge = 1: find cells to merge instead of painting and splitting
-int launch_stroke_visit(void* stream, const StrokeItem* items, uint32_t n, const StrokeArgs& a,
-                        const void* stamps, const void* rec, void* pay, uint64_t n_nodes,
-                        StrokeItem* next, uint32_t* next_count, uint32_t next_cap,
-                        StrokeItem* pend, void* pend_pay, uint32_t* pend_count, uint32_t pend_cap,
+// `levels` levels of a stroke's walk (cvx_stroke.hip) from n cells: items, or
+// nullptr for the roots.  counts[0] holds n; level l leaves its children's
+// count in counts[l + 1] and them in lists + (l & 1) cap (two lists of cap
+// cells).  merge = 1: find cells to merge instead of painting and splitting.
+int launch_stroke_visit(void* stream, uint32_t levels, const StrokeItem* items, uint32_t n,
+                        const StrokeArgs& a, const void* stamps, const void* rec, void* pay,
+                        uint64_t n_nodes, StrokeItem* lists, uint32_t cap, uint32_t* counts,
+                        StrokePend* pend, uint32_t* pend_count, uint32_t pend_cap,
                         uint32_t merge);
 
 }  // namespace cvx
