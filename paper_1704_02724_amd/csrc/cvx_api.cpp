@@ -487,14 +487,14 @@ int render_launch(cvx_ctx* ctx, const cvx_view* views, int n_views, void* out_de
     dv.max_depth = c.depth;
     for (int k = 0; k < 3; ++k) {
       dv.o[k] = (v.eye[k] - c.desc.origin[k]) / c.desc.root_edge;
-      dv.right[k] = v.right[k];
-      dv.up[k] = v.up[k];
+      // fwd + (2 (x + 1/2) / W - 1) tan_x right + (1 - 2 (y + 1/2) / H) tan_y up,
+      // each product rounded once
       dv.fwd[k] = v.fwd[k];
+      dv.dirx[k] = (double)(2.0L * v.tan_half_fov_x * v.right[k] / v.W);
+      dv.diry[k] = (double)(-2.0L * v.tan_half_fov_y * v.up[k] / v.H);
     }
-    dv.tan_x = v.tan_half_fov_x;
-    dv.tan_y = v.tan_half_fov_y;
-    dv.two_w = 2.0 / (double)v.W;
-    dv.two_h = 2.0 / (double)v.H;
+    dv.cx = 0.5 - 0.5 * (double)v.W;
+    dv.cy = 0.5 - 0.5 * (double)v.H;
     dv.W = v.W;
     dv.H = v.H;
     dv.out_off = v.out_offset_px;

@@ -146,23 +146,25 @@ __device__ __forceinline__ double rcp_nr(double x) {
   return __builtin_fabs(x) < 0x1p-1000 ? __builtin_copysign(__builtin_inf(), x) : r;
 }
 
+// The same without the inf: NaN for |x| < 2^-1022 or so.
+__device__ __forceinline__ double rcp_nz(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  for (int i = 0; i < 2; ++i) r = __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
+  return r;
+}
+
 // FP64 unit direction of pixel (x, y) in the public convention
-// (normalize(fwd + u right + v up), u and v from the pixel centre), no
-// contraction.  The divisions by the image size are products with the
-// view's 2/W and 2/H (each rounded once) and the normalisation multiplies by
-// a reciprocal square root of the squared norm: each component stays within
-// a few FP64 ulp of the convention's division form, far inside the 1e-12
-// band in which crossings count as ambiguous.
+// (normalize(fwd + u right + v up), u and v from the pixel centre), from the
+// view's affine form of it about the image centre (the products with the image
+// sizes and tangents rounded once on the host, the pixel's place exact).  Each
+// component stays within a few FP64 ulp of the convention's division form, far
+// inside the 1e-12 band in which crossings count as ambiguous.
 __device__ __forceinline__ V3<double> ray_dir(const DView& v, uint32_t x, uint32_t y) {
-#pragma clang fp contract(off)
-  double u = (((double)x + 0.5) * v.two_w - 1.0) * v.tan_x;
-  double w = (1.0 - ((double)y + 0.5) * v.two_h) * v.tan_y;
-  double d[3], n2 = 0.0;
-  for (int k = 0; k < 3; ++k) {
-    d[k] = v.fwd[k] + u * v.right[k];
-    d[k] = d[k] + w * v.up[k];
-    n2 += d[k] * d[k];
-  }
+  const double px = (double)x + v.cx, py = (double)y + v.cy;
+  double d[3];
+  for (int k = 0; k < 3; ++k)
+    d[k] = __builtin_fma(py, v.diry[k], __builtin_fma(px, v.dirx[k], v.fwd[k]));
+  const double n2 = __builtin_fma(d[2], d[2], __builtin_fma(d[1], d[1], d[0] * d[0]));
   const double rn = rsq_nr(n2);
   return V3<double>{d[0] * rn, d[1] * rn, d[2] * rn};
 }
@@ -235,6 +237,49 @@ __device__ __forceinline__ uint2 ld_pay_t(const void* pay, uint32_t i) {
   const u32x2_t x = *(gpay_t)((const __attribute__((address_space(1))) char*)pay + (i << 3));
   return make_uint2(x.x, x.y);
 }
+
+// Loads of the traversal loop.  BUFFER: pools of at most 2^28 nodes that one
+// wavefront-uniform view names are read as structured buffers: the instruction
+// takes the node id itself (no address arithmetic) and returns 0 beyond the
+// pool (so a null link needs no substitute).  Three vector instructions of a
+// leaf step less.
+typedef int i32x4_t __attribute__((ext_vector_type(4)));
+__device__ u32x4_t buffer_load4(i32x4_t rsrc, int index, int offset, int soffset,
+                                int aux) __asm("llvm.amdgcn.struct.buffer.load.v4i32");
+__device__ u32x2_t buffer_load2(i32x4_t rsrc, int index, int offset, int soffset,
+                                int aux) __asm("llvm.amdgcn.struct.buffer.load.v2i32");
+template <bool SMALL, bool BUFFER>
+struct PoolLoads {
+  const void* rec;
+  const void* pay;
+  __device__ __forceinline__ explicit PoolLoads(const DView& v) : rec(v.rec), pay(v.pay) {}
+  __device__ __forceinline__ uint32_t id(bool null, uint32_t n) const { return null ? 0u : n; }
+  __device__ __forceinline__ uint4 record(bool null, uint32_t n) const {
+    return ld_rec_t<SMALL>(rec, id(null, n));
+  }
+  __device__ __forceinline__ uint2 payload(uint32_t n) const { return ld_pay_t<SMALL>(pay, n); }
+};
+template <bool SMALL>
+struct PoolLoads<SMALL, true> {
+  i32x4_t rec, pay;
+  // base address and stride, records, raw 32-bit format
+  static __device__ __forceinline__ i32x4_t buffer(const void* p, uint32_t stride, uint32_t n) {
+    const uint64_t a = (uint64_t)p;
+    return i32x4_t{(int)(uint32_t)a, (int)(((uint32_t)(a >> 32) & 0xffffu) | (stride << 16)), (int)n,
+                   0x00027000};
+  }
+  __device__ __forceinline__ explicit PoolLoads(const DView& v)
+      : rec(buffer(v.rec, 16u, v.n_nodes)), pay(buffer(v.pay, 8u, v.n_nodes)) {}
+  __device__ __forceinline__ uint32_t id(bool, uint32_t n) const { return n; }
+  __device__ __forceinline__ uint4 record(bool, uint32_t n) const {
+    const u32x4_t x = buffer_load4(rec, (int)n, 0, 0, 0);
+    return make_uint4(x.x, x.y, x.z, x.w);
+  }
+  __device__ __forceinline__ uint2 payload(uint32_t n) const {
+    const u32x2_t x = buffer_load2(pay, (int)n, 0, 0, 0);
+    return make_uint2(x.x, x.y);
+  }
+};
 
 // Descend from the current cell (r refined) to the leaf containing q; on a
 // mid-plane the child on the side the ray moves into is taken.  Returns false
@@ -316,7 +361,7 @@ __device__ __forceinline__ bool descend_int(const void* rec, uint32_t n_nodes, V
 
 // Cell of a ray start: through the top-level table when the view has one
 // (the node of depth <= L covering the depth-L cell of C), else the root.
-__device__ __forceinline__ void locate_top(const DView& v, const V3<uint32_t>& C, uint32_t& I,
+__device__ __forceinline__ void locate_top(const DViewHost& v, const V3<uint32_t>& C, uint32_t& I,
                                            uint32_t& dep, V3<uint32_t>& c, uint4& r) {
   const uint32_t D = v.max_depth;
   if (v.top_depth) {
@@ -484,15 +529,21 @@ struct LeafLoad<true> {
 // where a descent cannot be certified and where the frame has become too
 // coarse for the leaf (GUARD).
 //
-// Bound by vector instruction issue (and, in small launches, by the latency
-// of one iteration: the neighbour's record, from beyond the L2).  A leaf step
-// is 65 vector instructions, a descent 44 in the same iteration.  A frame of
-// far planes at depth + 8 with a bound per axis, separate cell indices and
-// plane offsets, and an iteration of its own per descent, took 94 and 45 and
-// measured (one MI355X, whole call, before / after) 1214 / 959 us on a
-// 1920x1080 stereo pair of a 33 M-node depth-24 canvas, 813 / 661 us on a
-// 1024x1024 view of depth-29 leaves and 605 / 534 us on a 2160x2160 stereo
-// pair whose rays stop at an opacity.
+// Bound by vector instruction issue (81 % of the rate a probe of its own
+// instruction mix reaches, on depth-24) and, in small launches, by the latency
+// of one iteration: the neighbour's record, from beyond the L2.  A leaf step
+// is 56 vector instructions, a descent 48 in the same iteration.  Whole calls
+// on one MI355X, in us:
+//                                             depth-24   zoomed    stereo
+//                                             stereo     depth-30  2160x2160
+//   94 + 45 instructions, a bound per axis,
+//   cell indices beside plane offsets, an
+//   iteration of its own per descent            1214       813       605
+//   this bookkeeping, 65 + 44                    959       661       534
+//   ray set-up from the view's prepared start,
+//   axis masks scalar, loads by node id          836       577       380
+// (the last line with the launch changes described at WorkQueue and
+// k_stage_views; the last step alone 888 / 605 / 397 before its loop part).
 // ----------------------------------------------------------------------------
 constexpr float CERT_K = 1.0f + 0x1p-21f + 0x1p-22f;  // 1 + 12 u
 constexpr float CERT_B = 2.25f;
@@ -506,27 +557,27 @@ constexpr float GUARD_MAX = 0x1p-10f;
 // so the guard is tested every GUARD_EVERY steps (and at every descent)
 constexpr uint32_t GUARD_EVERY = 16;
 
-// Per-lane LDS slot holding the FP64 eye, direction and reciprocal direction
-// of the lane's ray, [9][blockDim.x] doubles (component-major, so lanes read
+// Per-lane LDS slot holding the FP64 direction and reciprocal direction of the
+// lane's ray, [6][blockDim.x] doubles (component-major, so lanes read
 // consecutive words).  The FP32 traversal needs them only on its rare FP64
 // paths; keeping them here instead of in registers raises the number of
 // resident wavefronts.
 extern __shared__ double s_ray[];
+constexpr uint32_t kSlotDoubles = 6;
 
 typedef __attribute__((address_space(3))) double lds_f64;
 
 struct RaySlot {
   lds_f64* p;  // this lane's first component
   uint32_t stride;
-  __device__ __forceinline__ void put(const V3<double>& o, const V3<double>& d,
-                                      const V3<double>& inv) const {
-    p[0] = o.x; p[stride] = o.y; p[2 * stride] = o.z;
-    p[3 * stride] = d.x; p[4 * stride] = d.y; p[5 * stride] = d.z;
-    p[6 * stride] = inv.x; p[7 * stride] = inv.y; p[8 * stride] = inv.z;
+  __device__ __forceinline__ void put(const V3<double>& d, const V3<double>& inv) const {
+    p[0] = d.x; p[stride] = d.y; p[2 * stride] = d.z;
+    p[3 * stride] = inv.x; p[4 * stride] = inv.y; p[5 * stride] = inv.z;
   }
-  // component j (0-2 eye, 3-5 direction, 6-8 reciprocal direction), read
-  // through an opaque pointer so the load stays on the rare path that needs it
-  __device__ __forceinline__ double at(int j) const { return opaque(p)[j * stride]; }
+  // component k, read through an opaque pointer so the load stays on the rare
+  // path that needs it
+  __device__ __forceinline__ double dir(int k) const { return opaque(p)[k * stride]; }
+  __device__ __forceinline__ double inv(int k) const { return opaque(p)[(3 + k) * stride]; }
 };
 
 // Work of one wavefront in the refilling render kernel: the rays of up to
@@ -552,16 +603,18 @@ struct RefillJob {
 // contributes only the part before it, decided like an exit (certified, else
 // in FP64 from the exact exit plane), and the piece ends there; a piece that
 // does not start at the canvas entry locates its first leaf from its start
-// point (shared_start = false: not through the view's shared eye leaf).
+// point.  shared_start: the ray starts in the view's shared eye leaf (en.t0 = 0
+// then, and the rest of en is not read).
 template <bool TRACE, bool STATS, bool SMALL, bool REFILL = false, bool SPLIT = false>
 __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& o_in,
                           const V3<double>& d_in, const V3<double>& inv_in, const Entry& en_in,
                           const V3<bool>& up_in, Sink sk, Acc& acc, Out& out,
                           const RefillJob* job = nullptr, double t_end = 0.0,
-                          bool shared_start = true) {
+                          bool shared_start = false) {
   static_assert(!(REFILL && SPLIT), "chord pieces are traced one per lane");
   const void* rec = v.rec;
   const void* payp = v.pay;
+  const PoolLoads<SMALL, SMALL && !TRACE && !STATS> pool(v);
   const uint32_t D = v.max_depth;
   // T <= t_stop never holds without an opacity stop
   const float t_stop = v.alpha_stop < 1.0f ? v.t_stop : -1.0f;
@@ -598,11 +651,27 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
   uint32_t step = 0;
   // SPLIT: s-value of the piece's end and its error bound (BIGF: no end)
   float s_end = BIGF, e_end = 0.0f;
+  auto eye = [&](int k) __attribute__((always_inline)) -> double {
+    return get(V3<double>{v.o[0], v.o[1], v.o[2]}, k);
+  };
   // FP64 face plane of axis k ahead of the ray (back = 0) or, with back = the
   // cell's width, behind it: +-(E + 1 - back) 2^-D, exact
   auto plane = [&](int k, int32_t back) __attribute__((always_inline)) -> double {
     const double n = (double)((int32_t)get(E, k) - back) + 1.0;
     return ldexp(get(up, k) ? n : -n, -(int)D);
+  };
+  // what a frame at ray parameter te has besides E0 and S0
+  auto frame_at = [&](double te) __attribute__((always_inline)) {
+    s_ent = 0.0f;
+    beta = ldexpf(tR, (int)D - 50);
+    if constexpr (SPLIT) {
+      // (t_end - te) 2^D rounded to FP32 (2^-24 relative) after an FP64
+      // difference within beta
+      const bool has_end = t_end < __builtin_inf();
+      s_end = has_end ? (float)ldexp(t_end - te, (int)D) : BIGF;
+      e_end = has_end ? beta + __builtin_fabsf(s_end) * 0x1p-23f : 0.0f;
+    }
+    if (STATS) acc.rebase++;
   };
   // FP64 rebuild of the frame at ray parameter te (q = FP64 point); the
   // current cell I is descended first when it is refined.
@@ -633,55 +702,64 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
       const uint32_t b = ck < lo ? lo : (ck > lo + low ? lo + low : ck);
       const uint32_t fm = get(up, k) ? 0u : ~0u;
       const double X = ldexp((double)(b + (get(up, k) ? 1u : 0u)), -(int)D);  // exact
-      const double Tk = (X - slot.at(k)) * slot.at(6 + k);
+      const double Tk = (X - eye(k)) * slot.inv(k);
       set(S0, k, get(tD, k) == 0.0f ? BIGF : (float)ldexp(Tk - te, (int)D));
       set(E0, k, b ^ fm);
       set(E, k, (lo ^ fm) | low);
     }
-    s_ent = 0.0f;
-    beta = ldexpf(tR, (int)D - 50);
-    if constexpr (SPLIT) {
-      // (t_end - te) 2^D rounded to FP32 (2^-24 relative) after an FP64
-      // difference within beta
-      const bool has_end = t_end < __builtin_inf();
-      s_end = has_end ? (float)ldexp(t_end - te, (int)D) : BIGF;
-      e_end = has_end ? beta + __builtin_fabsf(s_end) * 0x1p-23f : 0.0f;
-    }
-    if (STATS) acc.rebase++;
+    frame_at(te);
   };
   // ray start: the FP64 entry point, the first leaf and the first frame (Rd =
-  // the canvas side R in FP64)
+  // the canvas side R in FP64).  shared: the view's shared eye leaf; its frame
+  // needs neither the entry point nor a rebase (the same values, prepared once
+  // per view; the slab test is skipped too).  tR: a bound of the parameters and
+  // plane distances on the chord.
   auto begin = [&](const V3<double>& o, const V3<double>& d, const V3<double>& inv,
-                   const Entry& en, const V3<bool>& up_, double Rd)
+                   const Entry& en, const V3<bool>& up_, double Rd, bool shared)
       __attribute__((always_inline)) -> bool {
-    slot.put(o, d, inv);
+    slot.put(d, inv);
     for (int k = 0; k < 3; ++k)
       set(tD, k, __builtin_fabs(get(d, k)) >= 0x1p-60 ? (float)__builtin_fabs(get(inv, k)) : 0.0f);
     anypar = tD.x == 0.0f || tD.y == 0.0f || tD.z == 0.0f;
-    tR = (float)(en.t1 + Rd + 1.0);
+    tR = (float)__builtin_fma(2.7320509, Rd, en.t0 + 1.0);
     up = up_;
     if constexpr (!REFILL)
       for (int k = 0; k < 3; ++k) upm[k] = lanes(get(up_, k));
     if constexpr (!REFILL) parm = lanes(anypar);
-    // first leaf: the view's shared eye leaf, else FP64 point location from
-    // the top-level table or the root array (descended to the leaf by the
-    // rebase)
-    for (int k = 0; k < 3; ++k) {
-      double qk = get(o, k) + en.t0 * get(d, k);
-      if (k == en.kin) qk = en.side ? Rd : 0.0;
-      set(q, k, qk < 0.0 ? 0.0 : (qk > Rd ? Rd : qk));
-    }
-    uint32_t dep = 0;
-    V3<uint32_t> c;
-    start_leaf(v, q, up, I, dep, c, r, shared_start);
-    c = flip(c, up);
-    if (STATS) acc.descent += dep;
-    lw = D - dep;
-    E = V3<uint32_t>{c.x << lw, c.y << lw, c.z << lw};
-    pay = make_uint2(0u, 0u);
     te_last = 0.0;
     bool lost = false;
-    rebase(en.t0, lost);
+    if (shared) {
+      I = v.start_node;
+      r = ld_rec_t<SMALL>(rec, I);
+      pay = ld_pay_t<SMALL>(payp, I);
+      lw = D - v.start_dep;
+      const uint32_t low = (1u << lw) - 1u;
+      for (int k = 0; k < 3; ++k) {
+        const uint32_t fm = get(up, k) ? 0u : ~0u;
+        set(E0, k, v.start_base[k] ^ fm);
+        set(E, k, ((v.start_c[k] << lw) ^ fm) | low);
+        const double dist = get(up, k) ? v.start_up[k] : v.start_dn[k];
+        set(S0, k, get(tD, k) == 0.0f ? BIGF : (float)(dist * __builtin_fabs(get(inv, k))));
+      }
+      if (STATS) acc.descent += v.start_dep;
+      frame_at(0.0);
+    } else {
+      // FP64 point location from the top-level table or the root array
+      // (descended to the leaf by the rebase)
+      for (int k = 0; k < 3; ++k) {
+        double qk = get(o, k) + en.t0 * get(d, k);
+        if (k == en.kin) qk = en.side ? Rd : 0.0;
+        set(q, k, qk < 0.0 ? 0.0 : (qk > Rd ? Rd : qk));
+      }
+      uint32_t dep = 0;
+      V3<uint32_t> c;
+      locate_top(v, deep_coords(q, up, v.R, D), I, dep, c, r);
+      c = flip(c, up);
+      if (STATS) acc.descent += dep;
+      lw = D - dep;
+      E = V3<uint32_t>{c.x << lw, c.y << lw, c.z << lw};
+      rebase(en.t0, lost);
+    }
     T = 1.0f;
     C = V3<float>{0.f, 0.f, 0.f};
     n_rec = 0;
@@ -716,24 +794,27 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
     px = (uint32_t)(t % v.tiles_x) * job->tile_w + l % job->tile_w;
     py = (uint32_t)(t / v.tiles_x) * job->tile_h + l / job->tile_w;
     if (px >= v.W || py >= v.H) return false;
-    // the view's sizes pass an opaque barrier here, so that their FP64
-    // conversions stay on this path instead of living (in vector registers)
-    // through the traversal loop
-    DView vr = v;
-    vr.W = opaque_s(v.W);
-    vr.H = opaque_s(v.H);
+    // (opaque: the FP64 conversion stays on this path instead of living in
+    // vector registers through the traversal loop)
     const double Rd = (double)opaque_s(v.R);
-    const V3<double> d = ray_dir(vr, px, py);
+    const V3<double> d = ray_dir(v, px, py);
     const V3<double> o{v.o[0], v.o[1], v.o[2]};
-    const V3<double> inv{rcp_nr(d.x), rcp_nr(d.y), rcp_nr(d.z)};
-    const Entry en = canvas_entry(o, d, inv, Rd);
+    const bool shared = v.start_ok != 0u;
+    V3<double> inv;
+    Entry en{0.0, 0.0, -1, 0, true};
+    if (shared) {
+      inv = V3<double>{rcp_nz(d.x), rcp_nz(d.y), rcp_nz(d.z)};
+    } else {
+      inv = V3<double>{rcp_nr(d.x), rcp_nr(d.y), rcp_nr(d.z)};
+      en = canvas_entry(o, d, inv, Rd);
+    }
     out.rgba[0] = out.rgba[1] = out.rgba[2] = out.rgba[3] = 0.0;
     out.flags = 0;
     if (!en.hit) {
       write_pixel();
       return false;
     }
-    if (!begin(o, d, inv, en, V3<bool>{d.x > 0.0, d.y > 0.0, d.z > 0.0}, Rd)) {
+    if (!begin(o, d, inv, en, V3<bool>{d.x > 0.0, d.y > 0.0, d.z > 0.0}, Rd, shared)) {
       write_pixel();
       return false;
     }
@@ -746,7 +827,7 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
     alive = begin_job_ray(threadIdx.x & 63u);
     wait_for = job->refill_min;
   } else {
-    if (!begin(o_in, d_in, inv_in, en_in, up_in, (double)v.R)) return;
+    if (!begin(o_in, d_in, inv_in, en_in, up_in, (double)v.R, shared_start)) return;
   }
   // REFILL: rounds of traversal; a round ends when wait_for lanes wait, then
   // the waiting lanes take the job's next rays (ranked by a ballot), and once
@@ -775,13 +856,11 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
       for (int k = 0; k < 3; ++k)
         set(S, k, __builtin_fmaf((float)(int32_t)(get(E, k) - get(E0, k)), get(tD, k), get(S0, k)));
       const float Smin = __builtin_fminf(S.x, __builtin_fminf(S.y, S.z));
-      // exit axis (ties to the lower axis) as its bit kbit (1, 2, 4), also
-      // held one-hot as lane masks mx, my (z when neither) for the selects
-      // below
-      const uint64_t bx = lanes(S.x == Smin);
-      bool mx = lane(bx);
-      bool my = lane(lanes(S.y == Smin) & ~bx);
-      uint32_t kbit = mx ? 1u : (my ? 2u : 4u);
+      // exit axis (ties to the lower axis): one-hot lane masks bx, by (z when
+      // neither) and its bit kbit (1, 2, 4)
+      uint64_t bx = lanes(S.x == Smin);
+      uint64_t by = lanes(S.y == Smin) & ~bx;
+      uint32_t kbit = 0;
       // ---- neighbour across the exit face: sibling, next root or G_3 link.
       // Its record load is issued as soon as the exit axis is known (again
       // after an FP64 decision), so that its latency overlaps the
@@ -789,6 +868,8 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
       uint32_t Ex = 0;  // E on the exit axis
       bool inner = false;
       auto neighbour = [&](uint4 rr) __attribute__((always_inline)) -> uint32_t {
+        const bool mx = lane(bx), my = lane(by);
+        kbit = mx ? 1u : (my ? 2u : 4u);
         Ex = mx ? E.x : (my ? E.y : E.z);
         // the sibling lies across the face when the normalised index is even;
         // siblings differ in the exit axis's octant bit only
@@ -807,45 +888,47 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
         return N;
       };
       // the canvas boundary has null links (CVX_NONE >= n_nodes) and so would
-      // a broken pool; a null neighbour's load reads node 0 instead
+      // a broken pool; a null neighbour loads nothing (or node 0)
       uint32_t Nn = neighbour(r);
-      uint32_t In = Nn < v.n_nodes ? Nn : 0u;
-      uint4 rn = ld_rec_t<SMALL>(rec, In);
+      uint64_t null = lanes(Nn >= v.n_nodes);
+      uint4 rn = pool.record(lane(null), Nn);
       // certified when two planes exceed the threshold (the minimum's own test
       // is always false, so this is the majority of the three)
       const float thr = __builtin_fmaf(Smin, CERT_K, CERT_B * beta);
       const uint64_t s0 = lanes(S.x > thr);
       const uint64_t s1 = lanes(S.y > thr);
       const uint64_t s2 = lanes(S.z > thr);
-      const bool cert = lane((s0 & s1) | (s2 & (s0 | s1)));
+      const uint64_t unsure = lanes(true) & ~((s0 & s1) | (s2 & (s0 | s1)));
       float Sx = Smin;  // exit plane value (the smallest one unless FP64 decides)
-      if (!cert) {
+      if (unsure) {
         // FP64 decision from the exact face planes, t = (X - o_k) / d_k with
         // the ray's reciprocal direction (as the FP64 caster does; an ulp or
-        // two changes a decision only inside the 1e-12 face band)
+        // two changes a decision only inside the 1e-12 face band).  A uniform
+        // branch: every leaf lane computes it, the uncertain ones take it, and
+        // the axis masks stay scalar.
+        const bool mine = lane(unsure);
         double best = __builtin_inf();
         int kb = __builtin_ctz(kbit);
 #pragma unroll 1
         for (int k = 0; k < 3; ++k) {
           const double tt =
-              get(tD, k) == 0.0f ? __builtin_inf() : (plane(k, 0) - slot.at(k)) * slot.at(6 + k);
+              get(tD, k) == 0.0f ? __builtin_inf() : (plane(k, 0) - eye(k)) * slot.inv(k);
           kb = tt < best ? k : kb;
           best = tt < best ? tt : best;
         }
-        kbit = 1u << kb;
-        mx = kb == 0;
-        my = kb == 1;
-        Sx = get(S, kb);
+        bx = (bx & ~unsure) | (lanes(kb == 0) & unsure);
+        by = (by & ~unsure) | (lanes(kb == 1) & unsure);
+        Sx = mine ? get(S, kb) : Smin;
         Nn = neighbour(ld_rec_t<SMALL>(rec, I));
-        In = Nn < v.n_nodes ? Nn : 0u;
-        rn = ld_rec_t<SMALL>(rec, In);
-        need64 = true;
-        out.flags |= CVX_RAYFLAG_FP64_EXIT;
-        if (STATS) acc.fp64_exit++;
+        null = lanes(Nn >= v.n_nodes);
+        rn = pool.record(lane(null), Nn);
+        if (mine) out.flags |= CVX_RAYFLAG_FP64_EXIT;
+        if (STATS) acc.fp64_exit += mine;
       }
+      need64 = lane(unsure);
       if (TRACE) {
         const double t = te_last + ldexp((double)Sx, -(int)D);
-        for (int k = 0; k < 3; ++k) out.end[k] = slot.at(k) + t * slot.at(3 + k);
+        for (int k = 0; k < 3; ++k) out.end[k] = eye(k) + t * slot.dir(k);
       }
       // SPLIT: does the piece end inside this leaf?  Certainly when the exit
       // lies beyond the end by more than both bounds, certainly not when it
@@ -861,7 +944,7 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
             cut = true;
           } else {
             const int kx = __builtin_ctz(kbit);
-            cut = (plane(kx, 0) - slot.at(kx)) * slot.at(6 + kx) > t_end;
+            cut = (plane(kx, 0) - eye(kx)) * slot.inv(kx) > t_end;
           }
         }
         Sl = cut ? s_end : Sx;
@@ -895,20 +978,20 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
       // composite, so the record load has the whole step to arrive
       __builtin_amdgcn_sched_barrier(0);
       // ---- move to the neighbour (stop: bitwise, lane masks, not a branch)
-      stop = (Nn >= v.n_nodes) | (T <= t_stop);
+      stop = lane(null) | (T <= t_stop);
       if (stop) {
         // a null link is the canvas boundary when the exit plane is
-        if (Nn >= v.n_nodes) {
-          const bool upk = mx ? up.x : (my ? up.y : up.z);
+        if (lane(null)) {
+          const bool upk = lane(bx) ? up.x : (lane(by) ? up.y : up.z);
           if (Ex + 1u != (upk ? v.R << D : 0u)) out.flags |= CVX_RAYFLAG_BAD_LINK;
         }
       }
       // a ray that stopped still runs the move below (its results are not
-      // used), on node 0 when its neighbour is null
+      // used)
       if (STATS) acc.outer += !inner && !stop;
-      I = In;
+      I = pool.id(lane(null), Nn);
       r = rn;
-      pay = ld_pay_t<SMALL>(payp, I);
+      pay = pool.payload(I);
       s_ent = Sx;
       kbe = kbit;
       // one base cell on along the exit axis, then the low bits of the new
@@ -916,10 +999,9 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
       // as wide as the cell that was left)
       lw = is_leaf(rn.x) ? (D | CVX_XLEAF) - rn.x : lw;
       const uint32_t low = __builtin_amdgcn_ubfe(~0u, 0u, lw);
-      const uint64_t gx = lanes(kbit == 1u), gy = lanes(kbit == 2u);
-      E.x = plus(E.x, gx) | low;
-      E.y = plus(E.y, gy) | low;
-      E.z = plus(E.z, ~(gx | gy)) | low;
+      E.x = plus(E.x, bx) | low;
+      E.y = plus(E.y, by) | low;
+      E.z = plus(E.z, ~(bx | by)) | low;
     }
     if (!is_leaf(r.x) && !need64 && !stop) {
       // ---- refined cell: one level down, in the same iteration as the leaf
@@ -951,8 +1033,8 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
         // (inside the pool for every validated pool; clamped, so that no other
         // one reads past it)
         I = __builtin_elementwise_min(r.x + oct, v.n_nodes - 1u);
-        r = ld_rec_t<SMALL>(rec, I);
-        pay = ld_pay_t<SMALL>(payp, I);
+        r = pool.record(false, I);
+        pay = pool.payload(I);
         // waits for the record here, so that an iteration without a descent
         // does not wait (for its payload) at the top of the loop
         r.x = opaque(r.x);
@@ -963,8 +1045,8 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
       // FP64 rebase at the near face (axis bit kbe) of the current cell
       const int kr = __builtin_ctz(kbe);
       const double Xp = plane(kr, (int32_t)(1u << lw));
-      const double te = (Xp - slot.at(kr)) * slot.at(6 + kr);
-      for (int k = 0; k < 3; ++k) set(q, k, k == kr ? Xp : slot.at(k) + te * slot.at(3 + k));
+      const double te = (Xp - eye(kr)) * slot.inv(kr);
+      for (int k = 0; k < 3; ++k) set(q, k, k == kr ? Xp : eye(k) + te * slot.dir(k));
       rebase(te, stop);
     }
     if (stop) {
@@ -1410,9 +1492,18 @@ __device__ void cast_ray(const DView& v, uint32_t px, uint32_t py, Sink sk, Acc&
   out.steps = 0;
   out.end[0] = out.end[1] = out.end[2] = 0.0;
   if (STATS) acc.rays++;
-  const V3<double> inv{rcp_nr(d.x), rcp_nr(d.y), rcp_nr(d.z)};
-  const Entry en = canvas_entry(o, d, inv, (double)v.R);
-  if (!en.hit) return;
+  // a shared eye leaf: the ray starts at the eye, inside the canvas
+  constexpr bool kShared = VAR == (int)CVX_VARIANT_FP32_REBASED && !SPLIT;
+  const bool shared = kShared && v.start_ok != 0u;
+  V3<double> inv;
+  Entry en{0.0, 0.0, -1, 0, true};
+  if (shared) {
+    inv = V3<double>{rcp_nz(d.x), rcp_nz(d.y), rcp_nz(d.z)};
+  } else {
+    inv = V3<double>{rcp_nr(d.x), rcp_nr(d.y), rcp_nr(d.z)};
+    en = canvas_entry(o, d, inv, (double)v.R);
+    if (!en.hit) return;
+  }
   const V3<bool> up{d.x > 0.0, d.y > 0.0, d.z > 0.0};
   if constexpr (SPLIT) {
     static_assert(VAR == (int)CVX_VARIANT_FP32_REBASED, "chord pieces: FP32_REBASED only");
@@ -1427,9 +1518,9 @@ __device__ void cast_ray(const DView& v, uint32_t px, uint32_t py, Sink sk, Acc&
                              ? en.t0 + span * (double)(67u * (piece + 1u) + 1u) / den
                              : __builtin_inf();
     cast_fp32<TRACE, STATS, SMALL, false, true>(v, slot, o, d, inv, ep, up, sk, acc, out, nullptr,
-                                                t_end, piece == 0);
+                                                t_end, piece == 0 && v.start_ok != 0u);
   } else if constexpr (VAR == (int)CVX_VARIANT_FP32_REBASED) {
-    cast_fp32<TRACE, STATS, SMALL>(v, slot, o, d, inv, en, up, sk, acc, out);
+    cast_fp32<TRACE, STATS, SMALL>(v, slot, o, d, inv, en, up, sk, acc, out, nullptr, 0.0, shared);
   } else if constexpr (VAR == (int)CVX_VARIANT_FP64_PLAIN) {
     if (v.fmt == CVX_LEAF_F64)
       cast_fp64<TRACE, STATS, SMALL, true>(v, d, inv, en, up, sk, acc, out);
@@ -1752,7 +1843,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CVX_CAST64_
 // table), when every ray of the view starts there (eye strictly inside the
 // canvas and off every plane of the deepest grid: the slab test then gives
 // t0 = 0 and the start point is the eye itself for every direction).
-__device__ __forceinline__ void view_start(const DView& v, DView& dst, uint32_t enable) {
+__device__ __forceinline__ void view_start(const DViewHost& v, DView& dst, uint32_t enable) {
   dst.start_ok = 0u;
   if (!enable) return;
   const double Rd = (double)v.R;
@@ -1775,6 +1866,12 @@ __device__ __forceinline__ void view_start(const DView& v, DView& dst, uint32_t 
   dst.start_c[0] = c.x;
   dst.start_c[1] = c.y;
   dst.start_c[2] = c.z;
+  for (int k = 0; k < 3; ++k) {
+    const double Q = ldexp(v.o[k], (int)v.max_depth);
+    dst.start_base[k] = get(C, k);
+    dst.start_up[k] = ((double)get(C, k) + 1.0) - Q;
+    dst.start_dn[k] = Q - (double)get(C, k);
+  }
   dst.start_ok = 1u;
 }
 
@@ -1809,16 +1906,18 @@ __global__ __launch_bounds__(256) void k_stage_views(StageViews s, DView* views,
       hdr->n_queues = s.n_queues;
     }
   }
+  constexpr uint32_t words = sizeof(DViewHost) / 4, stride = sizeof(DView) / 4;
   const uint32_t* src = (const uint32_t*)s.v;
   uint32_t* dst = (uint32_t*)(views + s.first);
-  for (uint32_t w = t; w < s.count * (uint32_t)(sizeof(DView) / 4); w += blockDim.x) dst[w] = src[w];
+  for (uint32_t w = t; w < s.count * words; w += blockDim.x)
+    dst[w / words * stride + w % words] = src[w];
   __syncthreads();
   if (t < s.count) view_start(s.v[t], views[s.first + t], enable);
 }
 
 template <int VAR, bool TRACE, bool STATS, bool OUT64>
 int launch_t(void* stream, const CastArgs& a, uint32_t wgs, uint32_t wg_size) {
-  const size_t lds = VAR == (int)CVX_VARIANT_FP32_REBASED ? 9u * sizeof(double) * wg_size : 0u;
+  const size_t lds = VAR == (int)CVX_VARIANT_FP32_REBASED ? kSlotDoubles * sizeof(double) * wg_size : 0u;
   if constexpr (VAR == (int)CVX_VARIANT_FP64_PLAIN && !TRACE && !STATS) {
     if (a.small_pools)
       hipLaunchKernelGGL((k_cast64<OUT64, true>), dim3(wgs), dim3(wg_size), lds,
@@ -1917,7 +2016,7 @@ int launch_stage_views(void* stream, const DView* host_views, uint32_t n_views,
   for (uint32_t i = 0; i < n_views; i += CVX_STAGE_VIEWS) {
     s.first = i;
     s.count = n_views - i < CVX_STAGE_VIEWS ? n_views - i : CVX_STAGE_VIEWS;
-    std::memcpy(s.v, host_views + i, s.count * sizeof(DView));
+    for (uint32_t j = 0; j < s.count; ++j) s.v[j] = host_views[i + j];
     hipLaunchKernelGGL(k_stage_views, dim3(1), dim3(256), 0, (hipStream_t)stream, s, views, hdr,
                        enable);
     const int e = (int)hipGetLastError();

@@ -122,15 +122,16 @@ inline uint32_t top_table_depth(uint32_t R, uint32_t depth) {
   return L;
 }
 
-// Per-view parameters in device memory (host computes them once per render).
-struct DView {
+// Per-view parameters (the host computes them once per render).
+struct DViewHost {
   const void* rec;
   const void* pay;
   uint32_t R, fmt, max_depth, tiles_x;
   double o[3];          // eye in root-edge units
-  double right[3], up[3], fwd[3];
-  double tan_x, tan_y;
-  double two_w, two_h;  // 2 / W and 2 / H, rounded once
+  // unnormalised direction of pixel (x, y): fwd + (x + cx) dirx + (y + cy) diry,
+  // x + cx and y + cy exact, counted from the image centre
+  double fwd[3], dirx[3], diry[3];
+  double cx, cy;        // (1 - W) / 2 and (1 - H) / 2
   uint32_t W, H;
   uint64_t out_off;
   uint64_t first_tile;  // prefix sum of tile counts over the views
@@ -139,13 +140,20 @@ struct DView {
   uint32_t n_nodes;     // node ids at or above this are never loaded
   uint32_t top_depth;   // 0: ray starts descend from the root array
   const uint32_t* top;  // (R 2^top_depth)^3 node ids, x fastest
-  // the leaf holding the eye when every ray of the view starts there (eye
-  // inside the canvas, off every plane of the deepest grid), written on the
-  // device before the cast; start_ok = 0: each ray locates its first leaf
-  uint32_t start_ok, start_node, start_dep;
-  uint32_t start_c[3];  // its integer coordinates at start_dep
   uint32_t pieces;      // chord pieces per ray (1: unsplit)
   float t_stop;         // 1 - alpha_stop, rounded once: the FP32 caster stops once T <= t_stop
+};
+
+// The same in device memory, with what the device adds: the leaf holding the
+// eye when every ray of the view starts there (eye inside the canvas, off
+// every plane of the deepest grid); start_ok = 0: each ray locates its first
+// leaf.
+struct DView : DViewHost {
+  uint32_t start_ok, start_node, start_dep;
+  uint32_t start_c[3];     // the leaf's integer coordinates at start_dep
+  uint32_t start_base[3];  // the eye's cell at the deepest level
+  uint32_t pad;
+  double start_up[3], start_dn[3];  // from the eye to that cell's upper and lower planes, cells
 };
 
 // Work queues: the work items (tiles or 64-ray chunks) are split into
@@ -178,7 +186,7 @@ struct StageViews {
   uint64_t total_work, n_rays;  // the call's header
   uint32_t n_views, n_queues;
   uint32_t first, count;        // the views of this launch
-  DView v[CVX_STAGE_VIEWS];
+  DViewHost v[CVX_STAGE_VIEWS];
 };
 static_assert(sizeof(StageViews) <= 4000, "kernel arguments are limited to 4 KB");
 
