@@ -21,7 +21,7 @@ struct GraphKey {
   uint32_t variant = ~0u, tw = 0, th = 0, wgs = 0, wg = 0, item_tiles = 1, refill_min = 0,
            pieces = 1;
   bool trace = false, stats = false, out64 = false, small = false, per_ray_start = false,
-       by_args = false;
+       by_args = false, root_leaves = false;
   const void* out = nullptr;
   const void* stats_ptr = nullptr;
   const void* views = nullptr;
@@ -32,6 +32,7 @@ struct GraphKey {
            split_tmp == o.split_tmp &&
            trace == o.trace && stats == o.stats && out64 == o.out64 && small == o.small &&
            per_ray_start == o.per_ray_start && by_args == o.by_args &&
+           root_leaves == o.root_leaves &&
            out == o.out && stats_ptr == o.stats_ptr && views == o.views;
   }
 };
@@ -365,7 +366,8 @@ namespace {
 
 // Launch shape and mode of one render call, from its options.
 struct RenderPlan {
-  uint32_t tw = 8, th = 8, wg = 256, wgs = 0;
+  uint32_t tw = 8, th = 8;
+  uint32_t wg = 0, wgs = 0;  // 0: chosen by the work (launch_shape)
   uint32_t item_tiles = 1, refill_min = 32;  // lane refill of the FP32 render (item_tiles > 1)
   uint32_t pieces = 1;  // chord pieces per ray of the FP32 render or trace (views that run to
                         // the canvas exit; 1: unsplit)
@@ -390,10 +392,10 @@ int render_check(cvx_ctx* ctx, const cvx_view* views, int n_views, const void* o
   p.th = o.tile_h ? o.tile_h : 8;
   if (p.tw * p.th != 64 || p.tw == 0 || p.th == 0)
     return fail(ctx, CVX_ERR_INVALID_ARG, "tile_w * tile_h must be 64");
-  p.wg = o.wg_size ? o.wg_size : 256;
-  if (p.wg != 64 && p.wg != 128 && p.wg != 256)
+  p.wg = o.wg_size;
+  if (p.wg != 0 && p.wg != 64 && p.wg != 128 && p.wg != 256)
     return fail(ctx, CVX_ERR_INVALID_ARG, "wg_size must be 64, 128 or 256");
-  p.wgs = o.workgroups ? o.workgroups : (uint32_t)ctx->n_cu * (2048u / p.wg);
+  p.wgs = o.workgroups;
   if (p.wgs > (1u << 20)) return fail(ctx, CVX_ERR_INVALID_ARG, "too many workgroups");
   if (o.top_lookup > 1) return fail(ctx, CVX_ERR_INVALID_ARG, "top_lookup must be 0 or 1");
   if (o.single_queue > 1) return fail(ctx, CVX_ERR_INVALID_ARG, "single_queue must be 0 or 1");
@@ -553,8 +555,11 @@ int render_launch(cvx_ctx* ctx, const cvx_view* views, int n_views, void* out_de
   a.refill_min = p.refill_min;
   a.pieces = p.pieces;
   a.small_pools = o.wide_offsets ? 0u : 1u;
-  for (int i = 0; i < n_views; ++i)
-    if (ctx->canvases[views[i].canvas_id].n_nodes > (1ull << 28)) a.small_pools = 0;
+  for (int i = 0; i < n_views; ++i) {
+    const DevCanvas& c = ctx->canvases[views[i].canvas_id];
+    if (c.n_nodes > (1ull << 28)) a.small_pools = 0;
+    if (c.desc.R > 1 || c.depth == 0) a.root_leaves = 1;
+  }
   if (tr) {
     a.ray_ids = tr->ray_ids;
     a.max_leaves = tr->max_leaves;
@@ -566,12 +571,17 @@ int render_launch(cvx_ctx* ctx, const cvx_view* views, int n_views, void* out_de
     a.trace_rgba = tr->rgba;
     a.end_point = tr->end_point;
   }
+  // Workgroups of one wavefront while every CU has few (its own LDS and L1
+  // share): a 333x217 view measured 97 us in the kernel against 105 with four,
+  // 128x128 90 / 99, 64x64 71 / 74; with a full machine they are even.
+  const uint32_t wg = p.wg ? p.wg : (H.total_work <= 8ull * ctx->n_cu ? 64u : 256u);
   // no more workgroups than there are work items for, to the next power of two
   // (a captured graph then serves view sets of about the same size)
   uint64_t want = 8;
-  while (want * (p.wg / 64u) < H.total_work) want *= 2;
-  const uint32_t wgs = (uint32_t)std::min<uint64_t>(p.wgs, want);
-  a.fixed_wgs = std::min<uint32_t>(wgs, (uint32_t)ctx->n_cu * (64u * resident_waves(o) / p.wg));
+  while (want * (wg / 64u) < H.total_work) want *= 2;
+  const uint32_t wgs = (uint32_t)std::min<uint64_t>(
+      p.wgs ? p.wgs : (uint32_t)ctx->n_cu * (2048u / wg), want);
+  a.fixed_wgs = std::min<uint32_t>(wgs, (uint32_t)ctx->n_cu * (64u * resident_waves(o) / wg));
   const bool stats = o.stats != nullptr;
   // a split render writes its pieces to the context's buffer, merged after
   bool merge = false;
@@ -604,7 +614,7 @@ int render_launch(cvx_ctx* ctx, const cvx_view* views, int n_views, void* out_de
     const hipEvent_t* ev = (const hipEvent_t*)o.cast_events;
     if (ev) CVX_HIP(hipEventRecord(ev[0], ctx->stream));
     le = cvx::launch_cast(ctx->stream, o.variant, tr != nullptr, stats, o.out_f64 != 0, a, wgs,
-                          p.wg);
+                          wg);
     if (le != hipSuccess) return hip_fail(ctx, (hipError_t)le, "k_cast");
     if (ev) CVX_HIP(hipEventRecord(ev[1], ctx->stream));
     if (merge) {
@@ -619,7 +629,7 @@ int render_launch(cvx_ctx* ctx, const cvx_view* views, int n_views, void* out_de
   key.tw = p.tw;
   key.th = p.th;
   key.wgs = wgs;
-  key.wg = p.wg;
+  key.wg = wg;
   key.item_tiles = p.item_tiles;
   key.refill_min = p.refill_min;
   key.pieces = p.pieces;
@@ -630,6 +640,7 @@ int render_launch(cvx_ctx* ctx, const cvx_view* views, int n_views, void* out_de
   key.small = a.small_pools != 0;
   key.per_ray_start = o.per_ray_start != 0;
   key.by_args = by_args;
+  key.root_leaves = a.root_leaves != 0;
   key.out = out_dev;
   key.stats_ptr = o.stats;
   key.views = st.d_views;
@@ -639,7 +650,7 @@ int render_launch(cvx_ctx* ctx, const cvx_view* views, int n_views, void* out_de
     int le = hipSuccess;
     if (!by_args) le = cvx::launch_view_starts(ctx->home, st.d_views, st.d_hdr, shared_start);
     if (le == hipSuccess)
-      le = cvx::launch_cast(ctx->home, o.variant, false, stats, o.out_f64 != 0, a, wgs, p.wg);
+      le = cvx::launch_cast(ctx->home, o.variant, false, stats, o.out_f64 != 0, a, wgs, wg);
     if (le == hipSuccess && merge)
       le = cvx::launch_merge_pieces(ctx->home, st.d_views, st.d_hdr, (uint32_t)n_views,
                                     ctx->d_split, out_dev, p.pieces);

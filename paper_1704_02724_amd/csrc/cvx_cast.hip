@@ -605,7 +605,12 @@ struct RefillJob {
 // does not start at the canvas entry locates its first leaf from its start
 // point.  shared_start: the ray starts in the view's shared eye leaf (en.t0 = 0
 // then, and the rest of en is not read).
-template <bool TRACE, bool STATS, bool SMALL, bool REFILL = false, bool SPLIT = false>
+// ROOTS = false: no view has a leaf of depth 0 (one root, refined), so the step
+// needs no test for it: one compare and a branch over the root-array code, 4 %
+// of a depth-24 or depth-30 view (836 / 801 us, 577 / 554) and 8 us of a 64x64
+// view, where each branch of a lone wavefront's iteration is latency.
+template <bool TRACE, bool STATS, bool SMALL, bool REFILL = false, bool SPLIT = false,
+          bool ROOTS = true>
 __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& o_in,
                           const V3<double>& d_in, const V3<double>& inv_in, const Entry& en_in,
                           const V3<bool>& up_in, Sink sk, Acc& acc, Out& out,
@@ -876,7 +881,7 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
         inner = __builtin_amdgcn_ubfe(Ex, lw, 1u) == 0u;
         const uint32_t link = mx ? rr.y : (my ? rr.z : rr.w);
         uint32_t N = inner ? I ^ kbit : link;
-        if (lw == D) {
+        if (ROOTS && lw == D) {
           asm volatile("");  // root array (rare): a branch, not selects
           inner = false;
           const bool upk = mx ? up.x : (my ? up.y : up.z);
@@ -1093,11 +1098,12 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
 // 256x256 view of FP64 leaves 190 / 114 us.  76 VGPRs: 6 wavefronts per SIMD
 // without spills (7 would spill 24 bytes per lane).
 // ----------------------------------------------------------------------------
-template <bool TRACE, bool STATS, bool SMALL, bool LEAF64>
+template <bool TRACE, bool STATS, bool SMALL, bool LEAF64, bool ROOTS>
 __device__ void cast_fp64(const DView& v, const V3<double>& d, const V3<double>& inv,
                           const Entry& en, const V3<bool>& up, Sink sk, Acc& acc, Out& out) {
   const double Rd = (double)v.R;
   const void* rec = v.rec;
+  const PoolLoads<SMALL, SMALL && !TRACE && !STATS> pool(v);
   const uint32_t D = v.max_depth;
   const bool use_stop = v.alpha_stop < 1.0f;
   V3<double> q;
@@ -1156,7 +1162,7 @@ __device__ void cast_fp64(const DView& v, const V3<double>& d, const V3<double>&
       bool inner = __builtin_amdgcn_ubfe(Ex, lw, 1u) == 0u;
       uint32_t Nn = mx ? r.y : (my ? r.z : r.w);
       Nn = inner ? I ^ (mx ? 1u : (my ? 2u : 4u)) : Nn;
-      if (lw == D) {
+      if (ROOTS && lw == D) {
         asm volatile("");  // root array (rare): a branch, not selects
         inner = false;
         const bool upk = mx ? up.x : (my ? up.y : up.z);
@@ -1165,8 +1171,8 @@ __device__ void cast_fp64(const DView& v, const V3<double>& d, const V3<double>&
         const uint32_t rs = mx ? 1u : (my ? v.R : v.R * v.R);
         Nn = ncr >= v.R ? CVX_NONE : (upk ? I + rs : I - rs);
       }
-      const uint32_t In = Nn < v.n_nodes ? Nn : 0u;
-      const uint4 rn = ld_rec_t<SMALL>(rec, In);
+      const bool null = Nn >= v.n_nodes;
+      const uint4 rn = pool.record(null, Nn);
       double len = ldexp(best - t_ent, (int)(D - lw));
       len = len > 0.0 ? len : 0.0;
       if (TRACE)
@@ -1182,14 +1188,14 @@ __device__ void cast_fp64(const DView& v, const V3<double>& d, const V3<double>&
       if (TRACE) record(sk, n_rec, I, len);
       if (TRACE || STATS) ++n_rec;
       __builtin_amdgcn_sched_barrier(0);
-      stop = (Nn >= v.n_nodes) | (use_stop & (1.0 - T >= (double)v.alpha_stop));
-      if (stop && Nn >= v.n_nodes) {
+      stop = null | (use_stop & (1.0 - T >= (double)v.alpha_stop));
+      if (stop && null) {
         // a null link is the canvas boundary when the exit plane is
         const bool upk = mx ? up.x : (my ? up.y : up.z);
         if (Ex + 1u != (upk ? v.R << D : 0u)) out.flags |= CVX_RAYFLAG_BAD_LINK;
       }
       if (STATS) acc.outer += !inner && !stop;
-      I = In;
+      I = null ? 0u : Nn;
       r = rn;
       pay = LeafLoad<LEAF64>::template load<SMALL>(v.pay, I);
       t_ent = best > t_ent ? best : t_ent;
@@ -1223,7 +1229,7 @@ __device__ void cast_fp64(const DView& v, const V3<double>& d, const V3<double>&
       // (inside the pool for every validated pool; clamped, so that no other
       // one reads past it)
       I = __builtin_elementwise_min(r.x + oct, v.n_nodes - 1u);
-      r = ld_rec_t<SMALL>(rec, I);
+      r = pool.record(false, I);
       pay = LeafLoad<LEAF64>::template load<SMALL>(v.pay, I);
       r.x = opaque(r.x);  // waits for the record here, not at the top of the loop
       if (STATS) acc.descent++;
@@ -1479,7 +1485,8 @@ __device__ void cast_local(const DView& v, const V3<double>& d, const Entry& en,
 // [0, R] is a plane), where the end test of one piece and the point location
 // of the next could round to different sides; with the factor 67 (no root
 // array side has it) the cut points are not dyadic.
-template <int VAR, bool TRACE, bool STATS, bool SMALL = false, bool SPLIT = false>
+template <int VAR, bool TRACE, bool STATS, bool SMALL = false, bool SPLIT = false,
+          bool ROOTS = true>
 __device__ void cast_ray(const DView& v, uint32_t px, uint32_t py, Sink sk, Acc& acc, Out& out,
                          uint32_t piece = 0, uint32_t pieces = 1) {
   const RaySlot slot{(lds_f64*)(s_ray + threadIdx.x), blockDim.x};
@@ -1520,12 +1527,13 @@ __device__ void cast_ray(const DView& v, uint32_t px, uint32_t py, Sink sk, Acc&
     cast_fp32<TRACE, STATS, SMALL, false, true>(v, slot, o, d, inv, ep, up, sk, acc, out, nullptr,
                                                 t_end, piece == 0 && v.start_ok != 0u);
   } else if constexpr (VAR == (int)CVX_VARIANT_FP32_REBASED) {
-    cast_fp32<TRACE, STATS, SMALL>(v, slot, o, d, inv, en, up, sk, acc, out, nullptr, 0.0, shared);
+    cast_fp32<TRACE, STATS, SMALL, false, false, ROOTS>(v, slot, o, d, inv, en, up, sk, acc, out,
+                                                        nullptr, 0.0, shared);
   } else if constexpr (VAR == (int)CVX_VARIANT_FP64_PLAIN) {
     if (v.fmt == CVX_LEAF_F64)
-      cast_fp64<TRACE, STATS, SMALL, true>(v, d, inv, en, up, sk, acc, out);
+      cast_fp64<TRACE, STATS, SMALL, true, ROOTS>(v, d, inv, en, up, sk, acc, out);
     else
-      cast_fp64<TRACE, STATS, SMALL, false>(v, d, inv, en, up, sk, acc, out);
+      cast_fp64<TRACE, STATS, SMALL, false, ROOTS>(v, d, inv, en, up, sk, acc, out);
   } else if constexpr (VAR == (int)CVX_VARIANT_FP32_NAIVE) {
     cast_naive<TRACE, STATS>(v, d, en, up, sk, acc, out);
   } else if constexpr (VAR == (int)CVX_VARIANT_FP32_CELL_LOCAL) {
@@ -1638,7 +1646,8 @@ struct WorkQueue {
 // t, piece j at t * pieces + j); each piece writes its colour and
 // transmittance to a.split_tmp[pixel * a.pieces + j] for k_merge_pieces.  In
 // trace mode the rows are (ray, piece) pairs, ray-major, a.pieces per ray.
-template <int VAR, bool TRACE, bool STATS, bool OUT64, bool SMALL = false, bool SPLIT = false>
+template <int VAR, bool TRACE, bool STATS, bool OUT64, bool SMALL = false, bool SPLIT = false,
+          bool ROOTS = true>
 __device__ __forceinline__ void cast_grid(const CastArgs& a) {
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t nv = a.hdr->n_views;
@@ -1664,7 +1673,7 @@ __device__ __forceinline__ void cast_grid(const CastArgs& a) {
       const uint32_t x = tx * a.tile_w + lane % a.tile_w, y = ty * a.tile_h + lane / a.tile_w;
       if (x < v.W && y < v.H) {
         Sink sk{nullptr, nullptr, nullptr, 0};
-        cast_ray<VAR, false, STATS, SMALL, SPLIT>(v, x, y, sk, acc, res, piece, v.pieces);
+        cast_ray<VAR, false, STATS, SMALL, SPLIT, ROOTS>(v, x, y, sk, acc, res, piece, v.pieces);
         const uint64_t pix = v.out_off + (uint64_t)y * v.W + x;
         if (SPLIT && v.pieces > 1) {
           ((float4*)a.split_tmp)[pix * a.pieces + piece] =
@@ -1785,10 +1794,10 @@ __global__ __launch_bounds__(256) void k_cast(CastArgs a) {
 // instances use k_cast).  The FP32 caster fits eight wavefronts per SIMD
 // without spills (its LDS slot, 72 B per lane, then fills 147 KB of a CU's
 // 160 KB).
-template <bool OUT64, bool SMALL>
+template <bool SMALL, bool ROOTS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CVX_CAST32_WAVES))) void k_cast32(
     CastArgs a) {
-  cast_grid<(int)CVX_VARIANT_FP32_REBASED, false, false, OUT64, SMALL>(a);
+  cast_grid<(int)CVX_VARIANT_FP32_REBASED, false, false, false, SMALL, false, ROOTS>(a);
 }
 
 // The FP32 render of chord pieces (views with pieces > 1; the others as
@@ -1833,10 +1842,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CVX_CAST32R
 
 // The FP64 caster keeps its scaled eye and reciprocal direction in registers
 // (they enter every step).
-template <bool OUT64, bool SMALL>
+template <bool OUT64, bool SMALL, bool ROOTS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CVX_CAST64_WAVES))) void k_cast64(
     CastArgs a) {
-  cast_grid<(int)CVX_VARIANT_FP64_PLAIN, false, false, OUT64, SMALL>(a);
+  cast_grid<(int)CVX_VARIANT_FP64_PLAIN, false, false, OUT64, SMALL, false, ROOTS>(a);
 }
 
 // The leaf holding the eye of view v, into dst (v's place in the device
@@ -1919,11 +1928,14 @@ template <int VAR, bool TRACE, bool STATS, bool OUT64>
 int launch_t(void* stream, const CastArgs& a, uint32_t wgs, uint32_t wg_size) {
   const size_t lds = VAR == (int)CVX_VARIANT_FP32_REBASED ? kSlotDoubles * sizeof(double) * wg_size : 0u;
   if constexpr (VAR == (int)CVX_VARIANT_FP64_PLAIN && !TRACE && !STATS) {
-    if (a.small_pools)
-      hipLaunchKernelGGL((k_cast64<OUT64, true>), dim3(wgs), dim3(wg_size), lds,
+    if (a.small_pools && !a.root_leaves)
+      hipLaunchKernelGGL((k_cast64<OUT64, true, false>), dim3(wgs), dim3(wg_size), lds,
+                         (hipStream_t)stream, a);
+    else if (a.small_pools)
+      hipLaunchKernelGGL((k_cast64<OUT64, true, true>), dim3(wgs), dim3(wg_size), lds,
                          (hipStream_t)stream, a);
     else
-      hipLaunchKernelGGL((k_cast64<OUT64, false>), dim3(wgs), dim3(wg_size), lds,
+      hipLaunchKernelGGL((k_cast64<OUT64, false, true>), dim3(wgs), dim3(wg_size), lds,
                          (hipStream_t)stream, a);
   } else if constexpr (VAR == (int)CVX_VARIANT_FP32_REBASED && TRACE && !STATS && !OUT64) {
     if (a.pieces > 1u)
@@ -1947,11 +1959,14 @@ int launch_t(void* stream, const CastArgs& a, uint32_t wgs, uint32_t wg_size) {
       else
         hipLaunchKernelGGL((k_cast32r<false>), dim3(wgs), dim3(wg_size), lds, (hipStream_t)stream,
                            a);
+    } else if (a.small_pools && !a.root_leaves) {
+      hipLaunchKernelGGL((k_cast32<true, false>), dim3(wgs), dim3(wg_size), lds,
+                         (hipStream_t)stream, a);
     } else if (a.small_pools) {
-      hipLaunchKernelGGL((k_cast32<OUT64, true>), dim3(wgs), dim3(wg_size), lds,
+      hipLaunchKernelGGL((k_cast32<true, true>), dim3(wgs), dim3(wg_size), lds,
                          (hipStream_t)stream, a);
     } else {
-      hipLaunchKernelGGL((k_cast32<OUT64, false>), dim3(wgs), dim3(wg_size), lds,
+      hipLaunchKernelGGL((k_cast32<false, true>), dim3(wgs), dim3(wg_size), lds,
                          (hipStream_t)stream, a);
     }
   }

@@ -209,6 +209,7 @@ struct CastArgs {
   uint32_t tile_w, tile_h;
   uint32_t fixed_wgs;    // the first workgroups of the grid, whose wavefronts have a fixed item
   uint32_t small_pools;  // every pool the views read has at most 2^28 nodes
+  uint32_t root_leaves;  // some view's canvas may have leaves of depth 0 (R > 1, or one leaf)
   // FP32 render with lane refill when item_tiles > 1: a work item is up to
   // item_tiles tiles of one view, and waiting lanes take its next rays once
   // refill_min lanes of the wavefront wait

@@ -43,3 +43,38 @@ def test_views_at_the_edges(sess, n):
     assert (alone[:, 3] > 0).any()
     for kw in (dict(), dict(use_graph=True), dict(use_graph=True), dict(noalloc=True)):
         np.testing.assert_array_equal(sess.render(views, **kw).cpu().numpy(), alone)
+
+
+@pytest.mark.parametrize("variant", ["fp32_rebased", "fp64_plain"])
+def test_graph_follows_the_canvas(sess, variant):
+    """The kernel depends on whether a canvas can have leaves of depth 0: a
+    replay after the canvas under the same views has changed, by an upload or
+    by an edit, and mixed views, render as an eager call does."""
+    from canvasgen.pool import LEAF_DTYPE
+    from editmodel import COARSEN
+    views = [make_view((0.4, 0.45, -0.4), (0.02, 0.03, 1.0), 0.5, 40, 24, canvas_id=9),
+             make_view((0.6, 0.3, 0.2), (0.3, 0.4, 0.8), 0.9, 16, 40, canvas_id=9,
+                       out_offset_px=960)]
+    one = trees.single_cell((0.2, 0.5, 0.9), 1.5, LEAF_RGBA8_F16)
+    two = trees.uniform_tree(1, 1, seed=4, leaf_format=LEAF_RGBA8_F16)
+    for cv in (trees.random_tree(1, 4, seed=7, leaf_format=LEAF_RGBA8_F16),
+               trees.random_tree(2, 3, seed=8, p_split=0.4, leaf_format=LEAF_RGBA8_F16),
+               one, two):
+        sess.upload(9, cv)
+        for vs in (views, [views[0], dict(views[1], canvas_id=1)],
+                   [views[0], dict(views[1], canvas_id=0)]):
+            ref = sess.render(vs, variant).cpu().numpy()
+            for _ in range(2):
+                got = sess.render(vs, variant, use_graph=True).cpu().numpy()
+                np.testing.assert_array_equal(got, ref)
+            for j, v in enumerate(vs):  # and each view as it is alone
+                alone = sess.render([dict(v, out_offset_px=0)], variant).cpu().numpy()
+                o = v["out_offset_px"]
+                np.testing.assert_array_equal(ref[o:o + len(alone)], alone)
+    # the refined root becomes a leaf of depth 0
+    leaf = np.zeros(1, LEAF_DTYPE[LEAF_RGBA8_F16])
+    leaf["r"], leaf["kappa"] = 255, np.float16(0.75).view(np.uint16)
+    sess.edit(9, [(COARSEN, 0, 0)], leaf)
+    got = sess.render(views, variant, use_graph=True).cpu().numpy()
+    np.testing.assert_array_equal(got, sess.render(views, variant).cpu().numpy())
+    assert got[:, 1].max() == 0.0 and got[:, 0].max() > 0.2
