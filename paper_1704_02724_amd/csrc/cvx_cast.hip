@@ -1959,15 +1959,10 @@ int launch_t(void* stream, const CastArgs& a, uint32_t wgs, uint32_t wg_size) {
       else
         hipLaunchKernelGGL((k_cast32r<false>), dim3(wgs), dim3(wg_size), lds, (hipStream_t)stream,
                            a);
-    } else if (a.small_pools && !a.root_leaves) {
-      hipLaunchKernelGGL((k_cast32<true, false>), dim3(wgs), dim3(wg_size), lds,
-                         (hipStream_t)stream, a);
-    } else if (a.small_pools) {
-      hipLaunchKernelGGL((k_cast32<true, true>), dim3(wgs), dim3(wg_size), lds,
-                         (hipStream_t)stream, a);
     } else {
-      hipLaunchKernelGGL((k_cast32<false, true>), dim3(wgs), dim3(wg_size), lds,
-                         (hipStream_t)stream, a);
+      auto* k = a.small_pools ? (a.root_leaves ? k_cast32<true, true> : k_cast32<true, false>)
+                              : (a.root_leaves ? k_cast32<false, true> : k_cast32<false, false>);
+      hipLaunchKernelGGL(k, dim3(wgs), dim3(wg_size), lds, (hipStream_t)stream, a);
     }
   }
   else
