@@ -800,24 +800,23 @@ bool leaf_ok(const void* payloads, uint64_t i, uint32_t fmt) {
 int ensure_mirror(cvx_ctx* ctx, DevCanvas& c) {
   if (c.mirror_ready) return CVX_OK;
   c.mirror.assign(c.n_nodes, CVX_FREE);
-  uint32_t* packed = nullptr;
-  CVX_HIP(hipMalloc((void**)&packed, std::max<uint64_t>(c.n_nodes, 1) * 4));
-  int le = cvx::launch_extract_x(ctx->stream, c.rec, c.n_nodes, packed);
-  hipError_t e = (hipError_t)le;
+  uint32_t* packed = nullptr;  // the counts, then the words
+  uint32_t counts[cvx::CVX_COUNT_WORDS] = {};
+  CVX_HIP(hipMalloc((void**)&packed, sizeof counts + std::max<uint64_t>(c.n_nodes, 1) * 4));
+  uint32_t* words = packed + cvx::CVX_COUNT_WORDS;
+  hipError_t e = hipMemsetAsync(packed, 0, sizeof counts, ctx->stream);
   if (e == hipSuccess)
-    e = hipMemcpyAsync(c.mirror.data(), packed, c.n_nodes * 4, hipMemcpyDeviceToHost, ctx->stream);
+    e = (hipError_t)cvx::launch_extract_x(ctx->stream, c.rec, c.n_nodes, packed, words);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(counts, packed, sizeof counts, hipMemcpyDeviceToHost, ctx->stream);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(c.mirror.data(), words, c.n_nodes * 4, hipMemcpyDeviceToHost, ctx->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
   (void)hipFree(packed);
   if (e != hipSuccess) return hip_fail(ctx, e, "reading the pool records back");
   c.leaves_at_depth.assign(64, 0);
-  c.n_refined = 0;
-  for (uint32_t x : c.mirror) {
-    if (x == CVX_FREE) continue;
-    if (x & 1u)
-      ++c.leaves_at_depth[(x >> 1) & 63u];
-    else
-      ++c.n_refined;
-  }
+  for (uint32_t d = 0; d <= CVX_MAX_DEPTH; ++d) c.leaves_at_depth[d] = counts[d];
+  c.n_refined = counts[cvx::CVX_COUNT_REFINED];
   c.free_groups.clear();
   c.mirror_ready = true;
   return CVX_OK;

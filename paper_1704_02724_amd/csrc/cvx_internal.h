@@ -228,7 +228,10 @@ struct CastArgs {
 // kernel launchers (cvx_upload.hip, cvx_cast.hip); return a hipError_t value
 int launch_top_table(void* stream, const void* rec, uint64_t n_nodes, uint32_t R, uint32_t L,
                      uint32_t* top);
-int launch_extract_x(void* stream, const void* rec, uint64_t n, uint32_t* out);
+// Counts of k_extract_x: leaves per depth, then the refined nodes.
+constexpr uint32_t CVX_COUNT_REFINED = 63, CVX_COUNT_WORDS = 64;
+static_assert(CVX_MAX_DEPTH < CVX_COUNT_REFINED, "one word per depth");
+int launch_extract_x(void* stream, const void* rec, uint64_t n, uint32_t* counts, uint32_t* out);
 int launch_scatter_records(void* stream, const uint32_t* ids, const uint32_t* xs, uint64_t n,
                            void* rec);
 int launch_scatter_payloads(void* stream, const uint32_t* ids, const void* src, uint64_t n,

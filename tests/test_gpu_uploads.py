@@ -177,3 +177,31 @@ def test_upload_refuses_what_the_host_check_refuses(sess, fmt, R, depth):
             assert e.value.code == rc and msg in str(e.value)
     assert refused >= 12
     np.testing.assert_array_equal(sess.render(view, variant).cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("name", ["R=2, gaps", "depth 30", "wide"])
+def test_first_edit_after_an_upload(sess, name):
+    """The first edit counts the leaves per depth on the device (the wide pool
+    has more nodes than one pass of that launch): one refined leaf gives the
+    records of a fresh upload, and merged again those of the first."""
+    from paper_1704_02724_amd import cvx
+    cv = dict((n, c) for n, c in _pools() if c.leaf_format == LEAF_RGBA8_F16)[name]
+    sess.upload(0, cv)
+    before = cvx.cvx_read_records(sess.ctx, 0)
+    x, _ = _walk(cv)
+    leaves = np.nonzero((x != FREE) & (x & 1 == 1) & (x >> 1 < cv.max_depth))[0]
+    if name == "wide":  # its leaves are at its max_depth: one more
+        cv.max_depth = 2
+        sess.upload(0, cv)
+        leaves = np.nonzero(x & 1)[0]
+    i, g = int(leaves[len(leaves) // 2]), (len(x) + 7) // 8 * 8
+    first = sess.edit(0, [(1, i, 0)], np.repeat(cv.leaves[:1], 8))
+    assert first[0] == g
+    edited = cvx.cvx_read_records(sess.ctx, 0)
+    nodes = np.concatenate([cv.nodes, np.full((g + 8 - len(x), 2), FREE, np.uint32)])
+    nodes[i, 0], nodes[g:, 0], nodes[g:, 1] = g, LEAF, i
+    cv.nodes = nodes
+    sess.upload(1, cv)
+    np.testing.assert_array_equal(edited, cvx.cvx_read_records(sess.ctx, 1))
+    sess.edit(0, [(2, i, 0)], cv.leaves[:1])
+    np.testing.assert_array_equal(cvx.cvx_read_records(sess.ctx, 0)[:len(x)], before)
