@@ -59,6 +59,7 @@ struct cvx_ctx {
   // the two frontier lists of the link rebuilds, kept from one edit to the next
   // (grown when a rebuild overflows them, to at most the refined nodes)
   void* d_links = nullptr;
+  void* d_edit = nullptr;  // block of a small batch of edits (kEditBlockMax bytes)
   uint64_t links_cap = 0;
   // blocks of the strokes' walks, kept from one to the next
   void* d_walk[2] = {nullptr, nullptr};
@@ -206,6 +207,7 @@ void cvx_destroy(cvx_ctx* ctx) {
   if (ctx->d_stage) (void)hipFree(ctx->d_stage);
   if (ctx->d_split) (void)hipFree(ctx->d_split);
   if (ctx->d_links) (void)hipFree(ctx->d_links);
+  if (ctx->d_edit) (void)hipFree(ctx->d_edit);
   for (void* p : ctx->d_walk)
     if (p) (void)hipFree(p);
   if (ctx->h_stage) (void)hipHostFree(ctx->h_stage);
@@ -831,6 +833,13 @@ struct DevBuf {
 
 // Counts of a link rebuild: the region roots, then one per level and the next.
 constexpr uint32_t kLinkCounts = 1 + CVX_MAX_DEPTH + 2;
+// Batches that refine or merge at most as many nodes, with as many payloads,
+// run in one workgroup.  Refined and merged again in a pool of 9 M nodes, us,
+// one workgroup against a launch per step: 8 nodes 84 : 209, 64 nodes 110 : 212,
+// 256 nodes 185 : 278, 512 nodes (4,096 payloads) 290 : 390, 2,000 nodes
+// 1,130 : 918; 8,192 payloads alone 130 : 92, and 1,024 either way the same.
+constexpr uint64_t kSmallPaints = 4096, kSmallChanged = 512;
+constexpr uint64_t kEditBlockMax = 1u << 20;  // bytes of the block kept between batches
 constexpr uint64_t kLinkListMin = 1u << 18;  // nodes a frontier list starts with
 
 // The edits of cvx_edit_pool on a present canvas (also the splits of a
@@ -945,6 +954,7 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
     // edit reads the device state back
     c.mirror_ready = false;
     c.mirror.clear();
+    c.top_stale = true;
     return hip_fail(ctx, e, where);
   };
   if (n_cur > c.cap_nodes) {
@@ -1000,7 +1010,8 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
   const uint64_t o_ids = section(4 * n_touched), o_xs = section(4 * n_touched);
   const uint64_t o_pids = section(4 * n_paint), o_psrc = section(lb * n_paint);
   const uint64_t o_ch = section(4 * n_changed), o_chd = section(4 * n_changed);
-  const uint64_t o_counts = section(4 * kLinkCounts);  // [0]: region roots; then per level
+  // [0]: region roots; then per level; then the state of k_edit_small
+  const uint64_t o_counts = section(4 * (kLinkCounts + 1));
   const uint64_t up_bytes = at;                        // the rest is written on the device
   const uint64_t o_roots = section(4 * 7 * n_changed), o_rootd = section(4 * 7 * n_changed);
   std::vector<uint8_t> blob(up_bytes, 0);
@@ -1028,7 +1039,7 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
     }
   }
 
-  DevBuf b_blob;
+  DevBuf b_blob;  // a large batch; the block of small ones is kept
   hipError_t e = hipSuccess;
   const char* where = "";
 #define STEP(call)                      \
@@ -1041,7 +1052,13 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
     e = (hipError_t)(call);             \
     if (e != hipSuccess) where = name;  \
   }
-  STEP(hipMalloc(&b_blob.p, std::max<uint64_t>(at, 16)));
+  bool kept = at <= kEditBlockMax;
+  if (kept && !ctx->d_edit && hipMalloc(&ctx->d_edit, kEditBlockMax) != hipSuccess) {
+    (void)hipGetLastError();
+    ctx->d_edit = nullptr;
+    kept = false;
+  }
+  if (!kept) STEP(hipMalloc(&b_blob.p, std::max<uint64_t>(at, 16)));
   if (e == hipSuccess && c.mark_cap < c.n_nodes) {
     // marks, grown with the pool
     if (c.mark) (void)hipFree(c.mark);
@@ -1056,17 +1073,61 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
     c.epoch = 0;
   }
   if (e != hipSuccess) return device_fail(e, where);
-  uint8_t* blk = (uint8_t*)b_blob.p;
+  uint8_t* blk = (uint8_t*)(kept ? ctx->d_edit : b_blob.p);
   STEP(hipMemcpyAsync(blk, blob.data(), up_bytes, hipMemcpyHostToDevice, ctx->stream));
-  LAUNCH(cvx::launch_scatter_records(ctx->stream, (const uint32_t*)(blk + o_ids),
-                                     (const uint32_t*)(blk + o_xs), n_touched, c.rec),
-         "k_scatter_records");
-  LAUNCH(cvx::launch_scatter_payloads(ctx->stream, (const uint32_t*)(blk + o_pids), blk + o_psrc,
-                                      n_paint, lb, c.pay, c.mark, c.epoch + 1u),
-         "k_scatter_payloads");
+  const bool small = n_changed && n_changed <= kSmallChanged && n_paint <= kSmallPaints;
+  // no frontier is larger than the refined nodes; most are far smaller, so
+  // the lists start small and a rebuild that overflows them runs again
+  const uint64_t most = c.n_refined + 1;
+  if (n_changed && ctx->links_cap < std::min<uint64_t>(most, kLinkListMin)) {
+    if (ctx->d_links) (void)hipFree(ctx->d_links);
+    ctx->d_links = nullptr;
+    ctx->links_cap = 0;
+    STEP(hipMalloc(&ctx->d_links, 2 * kLinkListMin * 4));
+    if (e == hipSuccess) ctx->links_cap = kLinkListMin;
+  }
+  if (small) {
+    cvx::EditArgs ea = {};
+    ea.ids = (const uint32_t*)(blk + o_ids);
+    ea.xs = (const uint32_t*)(blk + o_xs);
+    ea.pids = (const uint32_t*)(blk + o_pids);
+    ea.src = blk + o_psrc;
+    ea.changed = (const uint32_t*)(blk + o_ch);
+    ea.changed_depth = (const uint32_t*)(blk + o_chd);
+    ea.roots = (uint32_t*)(blk + o_roots);
+    ea.root_depth = (uint32_t*)(blk + o_rootd);
+    ea.counts = (uint32_t*)(blk + o_counts);
+    ea.state = ea.counts + kLinkCounts;
+    ea.frontiers = (uint32_t*)ctx->d_links;
+    ea.cap = (uint32_t)ctx->links_cap;
+    ea.mark = c.mark;
+    ea.rec = c.rec;
+    ea.pay = c.pay;
+    ea.n_nodes = c.n_nodes;
+    ea.n_touched = (uint32_t)n_touched;
+    ea.n_paint = (uint32_t)n_paint;
+    ea.n_changed = (uint32_t)n_changed;
+    ea.words = lb / 8;
+    ea.base = c.epoch + 1u;
+    ea.epoch = c.epoch + (uint32_t)n_paint + 1u;
+    ea.R = R;
+    ea.first_level = d_first;
+    ea.depth = depth;
+    LAUNCH(cvx::launch_edit_small(ctx->stream, ea), "k_edit_small");
+    ++c.epoch;
+  } else {
+    LAUNCH(cvx::launch_scatter_records(ctx->stream, (const uint32_t*)(blk + o_ids),
+                                       (const uint32_t*)(blk + o_xs), n_touched, c.rec),
+           "k_scatter_records");
+    LAUNCH(cvx::launch_scatter_payloads(ctx->stream, (const uint32_t*)(blk + o_pids), blk + o_psrc,
+                                        n_paint, lb, c.pay, c.mark, c.epoch + 1u),
+           "k_scatter_payloads");
+  }
   c.epoch += (uint32_t)n_paint;
   // top-level table for the new depth (record words only)
   const uint32_t L = cvx::top_table_depth(R, depth);
+  const bool new_top = L != c.top_depth || c.top_stale;
+  c.top_stale = false;
   if (e == hipSuccess && L != c.top_depth) {
     if (c.top) (void)hipFree(c.top);
     c.top = nullptr;
@@ -1077,7 +1138,8 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
       if (e == hipSuccess) c.top_depth = L;
     }
   }
-  if (e == hipSuccess && c.top_depth) {
+  // nodes refined or merged at its depth or below it leave the table as it is
+  if (e == hipSuccess && c.top_depth && (new_top || d_first < c.top_depth)) {
     int le = cvx::launch_top_table(ctx->stream, c.rec, c.n_nodes, R, c.top_depth, c.top);
     if (le != hipSuccess) { e = (hipError_t)le; where = "k_top_table"; }
   }
@@ -1088,24 +1150,27 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
   bool synced = false;
   if (n_changed) {
     uint32_t* counts = (uint32_t*)(blk + o_counts);
-    LAUNCH(cvx::launch_dirty_roots(ctx->stream, (const uint32_t*)(blk + o_ch),
-                                   (const uint32_t*)(blk + o_chd), n_changed, c.rec, R,
-                                   (uint32_t*)(blk + o_roots), (uint32_t*)(blk + o_rootd), counts,
-                                   c.n_nodes),
-           "k_dirty_roots");
-    // no frontier is larger than the refined nodes; most are far smaller, so
-    // the lists start small and a rebuild that overflows them runs again
-    const uint64_t most = c.n_refined + 1;
-    for (bool again = true; e == hipSuccess && again && depth > d_first;) {
-      again = false;
-      if (ctx->links_cap < std::min<uint64_t>(most, kLinkListMin)) {
-        if (ctx->d_links) (void)hipFree(ctx->d_links);
-        ctx->d_links = nullptr;
-        ctx->links_cap = 0;
-        STEP(hipMalloc(&ctx->d_links, 2 * kLinkListMin * 4));
-        if (e == hipSuccess) ctx->links_cap = kLinkListMin;
+    uint32_t level = d_first;  // the first whose links are not done
+    if (small) {
+      uint32_t got[kLinkCounts + 1] = {0};
+      STEP(hipMemcpyAsync(got, counts, sizeof(got), hipMemcpyDeviceToHost, ctx->stream));
+      STEP(hipStreamSynchronize(ctx->stream));
+      synced = e == hipSuccess;
+      level = got[kLinkCounts];
+      if (e == hipSuccess && (got[0] > 7 * n_changed || level < d_first)) {
+        e = hipErrorUnknown;
+        where = "k_edit_small";
       }
-      LAUNCH(cvx::launch_links(ctx->stream, d_first, depth - 1, c.rec, R,
+    } else {
+      LAUNCH(cvx::launch_dirty_roots(ctx->stream, (const uint32_t*)(blk + o_ch),
+                                     (const uint32_t*)(blk + o_chd), n_changed, c.rec, R,
+                                     (uint32_t*)(blk + o_roots), (uint32_t*)(blk + o_rootd), counts,
+                                     c.n_nodes),
+             "k_dirty_roots");
+    }
+    for (bool again = true; e == hipSuccess && again && depth > level;) {
+      again = false;
+      LAUNCH(cvx::launch_links(ctx->stream, level, depth - 1, c.rec, R,
                                (const uint32_t*)(blk + o_roots), (const uint32_t*)(blk + o_rootd),
                                counts, (uint32_t*)ctx->d_links, (uint32_t)ctx->links_cap,
                                counts + 1, c.n_nodes, c.mark, ++c.epoch),
@@ -1122,6 +1187,7 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
         where = "link frontier overflow";
       } else if (large > ctx->links_cap) {
         again = true;
+        level = d_first;
         (void)hipFree(ctx->d_links);
         ctx->d_links = nullptr;
         const uint64_t cap = std::min<uint64_t>(most, 2 * (uint64_t)large);

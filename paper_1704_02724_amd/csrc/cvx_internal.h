@@ -104,6 +104,7 @@ struct DevCanvas {
   // count per depth
   uint64_t cap_nodes = 0;
   bool mirror_ready = false;
+  bool top_stale = false;  // the top-level table may not be that of the records
   std::vector<uint32_t> mirror;
   std::vector<uint32_t> free_groups;
   std::vector<uint64_t> leaves_at_depth;
@@ -232,6 +233,19 @@ int launch_top_table(void* stream, const void* rec, uint64_t n_nodes, uint32_t R
 constexpr uint32_t CVX_COUNT_REFINED = 63, CVX_COUNT_WORDS = 64;
 static_assert(CVX_MAX_DEPTH < CVX_COUNT_REFINED, "one word per depth");
 int launch_extract_x(void* stream, const void* rec, uint64_t n, uint32_t* counts, uint32_t* out);
+// A small batch of edits (k_edit_small).  counts: region roots found, then
+// nodes per level; state: the level whose links are not done, depth if none is.
+struct EditArgs {
+  const uint32_t *ids, *xs, *pids;
+  const void* src;
+  const uint32_t *changed, *changed_depth;
+  uint32_t *roots, *root_depth, *counts, *state, *mark, *frontiers;
+  void *rec, *pay;
+  uint64_t n_nodes;
+  uint32_t n_touched, n_paint, n_changed, words, base, epoch, R, first_level, depth, cap;
+};
+constexpr uint32_t EDIT_LIST = 2048;
+int launch_edit_small(void* stream, const EditArgs& a);
 int launch_scatter_records(void* stream, const uint32_t* ids, const uint32_t* xs, uint64_t n,
                            void* rec);
 int launch_scatter_payloads(void* stream, const uint32_t* ids, const void* src, uint64_t n,
