@@ -229,13 +229,13 @@ int cvx_set_stream(cvx_ctx* ctx, void* hip_stream);
 /* Upload a canvas pool (Sec. 4.1.1-4.1.2): host arrays are read during the
  * call only.  The pool is validated (indices in range, children groups
  * 8-aligned, each node reached once, parents consistent, depth <= max_depth,
- * leaf indices < n_leaves, finite non-negative kappa), re-laid out on the
- * device into 16-byte node records plus a node-indexed payload array, and
- * the three outer-face neighbour links per node are built on the GPU level
- * by level.  A top-level table (for every cell of depth L <= 6, at most 2^18
- * cells, the node of depth <= L covering it) is built on the GPU too; ray
- * starts use it to skip the first L levels of their descent.  Replaces any pool under canvas_id only on success.  Returns
- * CVX_ERR_BAD_POOL for an invalid pool, CVX_ERR_OOM when the device lacks
+ * leaf indices < n_leaves, finite non-negative kappa) and laid out in one walk
+ * on the device, level by level: 16-byte node records with three outer-face
+ * neighbour links per node, and a node-indexed payload array.  A top-level
+ * table (for every cell of depth L <= 6, at most 2^18 cells, the node of depth
+ * <= L covering it) is built on the GPU too; ray starts use it to skip the first
+ * L levels of their descent.  Replaces any pool under canvas_id only on
+ * success.  Returns CVX_ERR_BAD_POOL for an invalid pool, CVX_ERR_OOM when the device lacks
  * room (checked before any allocation). Synchronous. */
 int cvx_upload_pool(cvx_ctx* ctx, int canvas_id, const cvx_canvas_desc* desc,
                     const cvx_node* nodes, uint64_t n_nodes, const void* leaves,

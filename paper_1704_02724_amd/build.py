@@ -21,15 +21,13 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     # machine-level loop-invariant code motion lifts constants of the per-ray
     # setup out of the persistent tile loop, where they stay live through the
-    # whole traversal; without it the FP32 render kernel needs 61 VGPRs
-    # instead of 64 (earlier versions of the loop spilled 8-12 bytes per lane
-    # with it) and keeps the same hot-loop instructions
+    # whole traversal, at the edge of what the occupancy allows: with it a
+    # depth-24 stereo frame took 658 us instead of 613, in FP64 740 instead of 437
     "-mllvm", "-disable-machine-licm",
     # the render loop is bound by vector instruction issue; the scheduler's
     # ILP strategy orders its independent instructions so that more of them
-    # issue back to back (same instructions, same registers and occupancy;
-    # 0.4-1.4 % faster on the depth-24 stereo workload over five interleaved
-    # comparisons with the default strategy)
+    # issue back to back.  Its max-memory-clause strategy, which gathers the
+    # loads, was 1.3 % slower on a depth-24 stereo frame and 4 % on a 64x64 view
     "-mllvm", "-amdgpu-sched-strategy=max-ilp",
 ]
 

@@ -45,9 +45,10 @@ struct cvx_ctx {
   int n_cu = 256;
   std::string err;
   DevCanvas canvases[CVX_MAX_CANVASES];
-  // a render call's header and view table, staged in one pinned host block
-  // and copied by one transfer into one device block: CastHeader, then
-  // stage_cap view records
+  // a render call's header and view table on the device (CastHeader, then
+  // stage_cap view records), and the pinned host block that they are written
+  // in; tables of many views are copied from there, small ones are kernel
+  // arguments
   void* d_stage = nullptr;
   void* h_stage = nullptr;
   size_t stage_cap = 0;

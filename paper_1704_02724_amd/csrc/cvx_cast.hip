@@ -1792,7 +1792,7 @@ __global__ __launch_bounds__(256) void k_cast(CastArgs a) {
 
 // Render-mode entry points with an occupancy target (trace and stats
 // instances use k_cast).  The FP32 caster fits eight wavefronts per SIMD
-// without spills (its LDS slot, 72 B per lane, then fills 147 KB of a CU's
+// without spills (its LDS slot, 48 B per lane, then takes 98 KB of a CU's
 // 160 KB).
 template <bool SMALL, bool ROOTS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CVX_CAST32_WAVES))) void k_cast32(
