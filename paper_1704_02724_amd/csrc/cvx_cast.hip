@@ -550,9 +550,17 @@ constexpr float CERT_B = 2.25f;
 // descents: 3 u for each value and u for the rounding of their difference
 constexpr float DESC_A = 0x1p-22f;
 // a frame serves a leaf while 16 u s + 2 beta, more than the error of a
-// segment's length, stays within 2^-10 of the leaf's edge
+// segment's length, stays within 2^-12 of the leaf's edge, and 2^-13 where a
+// descent leads into it.  The descent's is what counts: a ray that comes from
+// afar into fine leaves would go through them in the frame of its start.  With
+// 2^-10 for both, single pixels were up to 8e-4 off and small images further
+// from the 64-bit ones than with frames of 8 levels (64x64: 1.2e-5 against
+// 1.3e-6 relative; now 5.3e-7); 2^-14 gains little (a zoomed depth-30 view,
+// 64x64, a batch of thumbnails: 462 / 65 / 173 us with 2^-10, 512 / 67 /
+// 196 with 2^-13, 541 / 105 / 230 with 2^-14; depth-24 stereo 615 / 627 / 659).
 constexpr float GUARD_A = 0x1p-20f;
-constexpr float GUARD_MAX = 0x1p-10f;
+constexpr float GUARD_MAX = 0x1p-12f;
+constexpr float GUARD_DESC = 0x1p-13f;
 // s grows by at most sqrt(3) leaf edges per step through leaves of one size,
 // so the guard is tested every GUARD_EVERY steps (and at every descent)
 constexpr uint32_t GUARD_EVERY = 16;
@@ -1024,7 +1032,7 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
         sure &= lanes(__builtin_fabsf(diff) > __builtin_fmaf(DESC_A, G, e_sum));
       }
       // the frame must also be fine enough for the child
-      sure &= lanes(ldexpf(__builtin_fmaf(GUARD_A, s_ent, 2.0f * beta), 1 - (int)lw) <= GUARD_MAX);
+      sure &= lanes(ldexpf(__builtin_fmaf(GUARD_A, s_ent, 2.0f * beta), 1 - (int)lw) <= GUARD_DESC);
       need64 = !lane(sure);
       if (!need64) {
         // octant bits: the far child is the upper one where the ray goes up
