@@ -49,7 +49,8 @@ __device__ __forceinline__ uint32_t neighbour_of_parent(const uint4 r, uint32_t 
 // the message; it used to make this walk for every pool, one random record
 // after the other, and send its breadth-first order along.  An upload of 357,040
 // nodes took 1.36 ms and takes 0.44, of 33.4 M nodes 154 ms and 20: the copy of
-// the pool from pageable memory bounds it now, the kernels take 1.2 ms of the 20.
+// the pool from pageable memory bounds it now (of 56.5 M nodes the kernels take
+// 2.9 ms of 37).
 __device__ __forceinline__ bool bad_payload(const uint2* pay, uint64_t i, uint32_t fmt) {
   if (fmt == CVX_LEAF_RGBA8_F16) {
     const uint32_t h = pay[i].y & 0xffffu;  // negative (but not -0), or not finite
