@@ -515,55 +515,49 @@ struct LeafLoad<true> {
 //   sibling across face k          when bit lw of E_k is 0.
 // The far plane of the cell (the one ahead of the ray) has the s-value
 //   S_k = S0_k + (E_k - E0_k) / |d_k|,
-// E0_k the base cell that holds p0 and S0_k its far plane's s-value, computed
-// in FP64 and rounded once.  E_k >= E0_k for every cell the ray visits after
-// p0, so both terms are >= 0 and, u = 2^-24 (the FP32 roundings of N = E - E0,
-// of 1/|d|, of S0 and of the fused update),
-//   |S_k - exact| <= 3 u S_k + beta,   beta = 2^(D-50) tR (the FP64 rebase),
-// with no drift in the number of steps (unlike the per-step update analysed in
-// Sec. 6.3).  Exit = argmin S_k, certified when the two other planes exceed
-// Smin (1 + 12 u) + 2.25 beta, one threshold for all three axes; otherwise the
-// FP64 face planes decide.  A refined cell is descended by comparing the entry
-// s with the mid-plane s-values, certified with |N| in place of N.  FP64
-// rebuilds the frame ("rebase") at the ray's start, after an FP64 decision,
-// where a descent cannot be certified and where the frame has become too
-// coarse for the leaf (GUARD).
+// E0_k that of the frame's first leaf and S0_k its far plane's s-value, computed
+// in FP64 and rounded once.  With no drift in the number of steps (unlike the
+// per-step update analysed in Sec. 6.3),
+//   |S_k - exact| <= 2^-21 (S0_k + |E_k - E0_k| / |d_k|) + beta,
+//   beta = 2^(D-50) tR (the FP64 rebase),
+// which covers the FP32 roundings of S0, of 1/|d|, of N = E - E0 and of the
+// fused update.  Exit = argmin S_k, certified when the lower bounds of the two
+// other planes exceed the minimum's upper bound; otherwise the FP64 face planes
+// decide.  A refined cell is descended by comparing the entry s with the
+// mid-plane s-values (certified likewise).  FP64 rebuilds the frame ("rebase")
+// at the ray's start, after an FP64 decision, where a descent cannot be
+// certified or goes more than FRAME_LEVELS below the frame's first leaf, and
+// where the bound on a segment's length has passed GUARD_MAX of the leaf's edge.
 //
-// Bound by vector instruction issue (81 % of the rate a probe of its own
-// instruction mix reaches, on depth-24) and, in small launches, by the latency
-// of one iteration: the neighbour's record, from beyond the L2.  A leaf step
-// is 56 vector instructions, a descent 48 in the same iteration.  Whole calls
-// on one MI355X, in us:
+// Images depend on where frames begin and on what their rounded values are
+// counted from, in single pixels by up to 2e-3 of an image's root mean square,
+// and these are the frames that images have been made with.  Counted from the
+// base cell that holds p0, so that no difference E - E0 is negative and one
+// threshold serves the three axes (56 instructions a leaf step in place of 72),
+// and with a guard of 2^-12 (2^-13 at descents) in place of the level limit,
+// the median error against 64 bits was half of it, but in 4 of 40 views of
+// 64x64 it was 1.9 to 3.9 times as large.
+//
+// Bound by vector instruction issue and, in small launches, by the latency of
+// one iteration: the neighbour's record, from beyond the L2.  A leaf step is 72
+// vector instructions, a descent 50 in the same iteration.  Whole calls on one
+// MI355X, in us (the second line with the launch changes described at WorkQueue
+// and k_stage_views):
 //                                             depth-24   zoomed    stereo
 //                                             stereo     depth-30  2160x2160
-//   94 + 45 instructions, a bound per axis,
-//   cell indices beside plane offsets, an
-//   iteration of its own per descent            1214       813       605
-//   this bookkeeping, 65 + 44                    959       661       534
-//   ray set-up from the view's prepared start,
-//   axis masks scalar, loads by node id          836       577       380
-// (the last line with the launch changes described at WorkQueue and
-// k_stage_views; the last step alone 888 / 605 / 397 before its loop part).
+//   94 + 45 instructions, cell indices beside
+//   plane offsets, an iteration of its own
+//   per descent, all rays set up from scratch   1210       813       605
+//   this bookkeeping, set-up from the view's
+//   prepared start, scalar axis masks, loads
+//   by node id                                   868       586       392
 // ----------------------------------------------------------------------------
-constexpr float CERT_K = 1.0f + 0x1p-21f + 0x1p-22f;  // 1 + 12 u
-constexpr float CERT_B = 2.25f;
-// descents: 3 u for each value and u for the rounding of their difference
-constexpr float DESC_A = 0x1p-22f;
-// a frame serves a leaf while 16 u s + 2 beta, more than the error of a
-// segment's length, stays within 2^-12 of the leaf's edge, and 2^-13 where a
-// descent leads into it.  The descent's is what counts: a ray that comes from
-// afar into fine leaves would go through them in the frame of its start.  With
-// 2^-10 for both, single pixels were up to 8e-4 off and small images further
-// from the 64-bit ones than with frames of 8 levels (64x64: 1.2e-5 against
-// 1.3e-6 relative; now 5.3e-7); 2^-14 gains little (a zoomed depth-30 view,
-// 64x64, a batch of thumbnails: 462 / 65 / 173 us with 2^-10, 512 / 67 /
-// 196 with 2^-13, 541 / 105 / 230 with 2^-14; depth-24 stereo 615 / 627 / 659).
-constexpr float GUARD_A = 0x1p-20f;
-constexpr float GUARD_MAX = 0x1p-12f;
-constexpr float GUARD_DESC = 0x1p-13f;
-// s grows by at most sqrt(3) leaf edges per step through leaves of one size,
-// so the guard is tested every GUARD_EVERY steps (and at every descent)
-constexpr uint32_t GUARD_EVERY = 16;
+// certification bound per plane value: 1.0625 (2^-21 G + beta) plus 2^-23 G for
+// the FP32 rounding of the comparison (G >= |value|), folded into one fma
+constexpr float CERT_A = 0x1p-21f * 1.0625f + 0x1p-23f;
+constexpr float CERT_B = 1.0625f;
+constexpr uint32_t FRAME_LEVELS = 8;
+constexpr float GUARD_MAX = 0x1p-10f;
 
 // Per-lane LDS slot holding the FP64 direction and reciprocal direction of the
 // lane's ray, [6][blockDim.x] doubles (component-major, so lanes read
@@ -604,8 +598,7 @@ struct RefillJob {
 // FP32_REBASED traversal of one lane: one ray (REFILL = false: o, d, inv,
 // en, up describe it) or, REFILL = true, the rays a RefillJob hands out one
 // after another, each written to its pixel when it ends.  The per-ray
-// arithmetic is the same in both, so both give the same pixels (up to the
-// guard, which a refilled lane tests at every step).
+// arithmetic is the same in both, so both give the same pixels.
 // SPLIT = true: the ray's chord is cut at ray parameter t_end (the end of a
 // chord piece; infinity for the last piece): the leaf holding t_end
 // contributes only the part before it, decided like an exit (certified, else
@@ -649,11 +642,12 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
   uint32_t I = 0;
   uint32_t lw = 0;               // the cell is 2^lw base cells wide
   V3<uint32_t> E{0, 0, 0};       // its last base cell per axis, normalised
-  V3<uint32_t> E0{0, 0, 0};      // the frame's reference base cell
+  V3<uint32_t> E0{0, 0, 0};      // E of the frame's first leaf
+  uint32_t lw_min = 0;           // the finest cell that the frame serves
   uint4 r;
   uint2 pay = make_uint2(0u, 0u);
   V3<float> S0{0.f, 0.f, 0.f};
-  float s_ent = 0.0f, beta = 0.0f;
+  float s_ent = 0.0f, e_ent = 0.0f, betac = 0.0f;  // betac = CERT_B beta
   double te_last = 0.0;  // trace mode: ray parameter of the last rebase
   float T = 1.0f;
   V3<float> C{0.f, 0.f, 0.f};
@@ -673,10 +667,14 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
     const double n = (double)((int32_t)get(E, k) - back) + 1.0;
     return ldexp(get(up, k) ? n : -n, -(int)D);
   };
-  // what a frame at ray parameter te has besides E0 and S0
+  // what a frame at ray parameter te has besides S0
   auto frame_at = [&](double te) __attribute__((always_inline)) {
+    E0 = E;
+    lw_min = __builtin_elementwise_sub_sat(lw, FRAME_LEVELS);
     s_ent = 0.0f;
-    beta = ldexpf(tR, (int)D - 50);
+    const float beta = ldexpf(tR, (int)D - 50);
+    e_ent = beta;
+    betac = beta * CERT_B;
     if constexpr (SPLIT) {
       // (t_end - te) 2^D rounded to FP32 (2^-24 relative) after an FP64
       // difference within beta
@@ -695,8 +693,7 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
     V3<uint32_t> cr{(uint32_t)((int32_t)E.x >> lw), (uint32_t)((int32_t)E.y >> lw),
                     (uint32_t)((int32_t)E.z >> lw)};
     cr = flip(cr, up);  // true indices
-    V3<uint32_t> Cd = deep_coords(q, up, v.R, D);
-    if (!descend_int(rec, v.n_nodes, Cd, D, I, dep, cr, r)) {
+    if (!descend_int(rec, v.n_nodes, deep_coords(q, up, v.R, D), D, I, dep, cr, r)) {
       // a node index outside the pool, which no validated pool has
       out.flags |= CVX_RAYFLAG_BAD_LINK;
       stop = true;
@@ -710,17 +707,19 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
     // the bound)
 #pragma unroll 1
     for (int k = 0; k < 3; ++k) {
-      // the base cell of p0, inside the leaf
-      const uint32_t lo = get(cr, k) << lw, ck = get(Cd, k);
-      const uint32_t b = ck < lo ? lo : (ck > lo + low ? lo + low : ck);
+      const uint32_t lo = get(cr, k) << lw;
       const uint32_t fm = get(up, k) ? 0u : ~0u;
-      const double X = ldexp((double)(b + (get(up, k) ? 1u : 0u)), -(int)D);  // exact
+      const double X = ldexp((double)(get(up, k) ? lo + low + 1u : lo), -(int)D);  // exact
       const double Tk = (X - eye(k)) * slot.inv(k);
       set(S0, k, get(tD, k) == 0.0f ? BIGF : (float)ldexp(Tk - te, (int)D));
-      set(E0, k, b ^ fm);
       set(E, k, (lo ^ fm) | low);
     }
     frame_at(te);
+  };
+  // error bound of the plane of axis k that lies Nf base cells past E0's
+  auto bound = [&](float Nf, int k) __attribute__((always_inline)) -> float {
+    const float G = __builtin_fmaf(__builtin_fabsf(Nf), get(tD, k), get(S0, k));
+    return __builtin_fmaf(CERT_A, G, betac);
   };
   // ray start: the FP64 entry point, the first leaf and the first frame (Rd =
   // the canvas side R in FP64).  shared: the view's shared eye leaf; its frame
@@ -732,7 +731,7 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
       __attribute__((always_inline)) -> bool {
     slot.put(d, inv);
     for (int k = 0; k < 3; ++k)
-      set(tD, k, __builtin_fabs(get(d, k)) >= 0x1p-60 ? (float)__builtin_fabs(get(inv, k)) : 0.0f);
+      set(tD, k, __builtin_fabs(get(d, k)) >= 0x1p-60 ? 1.0f / __builtin_fabsf((float)get(d, k)) : 0.0f);
     anypar = tD.x == 0.0f || tD.y == 0.0f || tD.z == 0.0f;
     tR = (float)__builtin_fma(2.7320509, Rd, en.t0 + 1.0);
     up = up_;
@@ -749,7 +748,6 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
       const uint32_t low = (1u << lw) - 1u;
       for (int k = 0; k < 3; ++k) {
         const uint32_t fm = get(up, k) ? 0u : ~0u;
-        set(E0, k, v.start_base[k] ^ fm);
         set(E, k, ((v.start_c[k] << lw) ^ fm) | low);
         const double dist = get(up, k) ? v.start_up[k] : v.start_dn[k];
         set(S0, k, get(tD, k) == 0.0f ? BIGF : (float)(dist * __builtin_fabs(get(inv, k))));
@@ -865,9 +863,12 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
     bool need64 = false, stop = false;
     if (is_leaf(r.x)) {
       // ---- leaf: s-values of its far planes, exit face
-      V3<float> S;
-      for (int k = 0; k < 3; ++k)
-        set(S, k, __builtin_fmaf((float)(int32_t)(get(E, k) - get(E0, k)), get(tD, k), get(S0, k)));
+      V3<float> S, eb;
+      for (int k = 0; k < 3; ++k) {
+        const float Nf = (float)(int32_t)(get(E, k) - get(E0, k));
+        set(S, k, __builtin_fmaf(Nf, get(tD, k), get(S0, k)));
+        set(eb, k, bound(Nf, k));
+      }
       const float Smin = __builtin_fminf(S.x, __builtin_fminf(S.y, S.z));
       // exit axis (ties to the lower axis): one-hot lane masks bx, by (z when
       // neither) and its bit kbit (1, 2, 4)
@@ -879,11 +880,13 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
       // after an FP64 decision), so that its latency overlaps the
       // certification and the composite instead of stalling the move.
       uint32_t Ex = 0;  // E on the exit axis
+      float ex = 0.0f;  // error bound of the exit plane
       bool inner = false;
       auto neighbour = [&](uint4 rr) __attribute__((always_inline)) -> uint32_t {
         const bool mx = lane(bx), my = lane(by);
         kbit = mx ? 1u : (my ? 2u : 4u);
         Ex = mx ? E.x : (my ? E.y : E.z);
+        ex = mx ? eb.x : (my ? eb.y : eb.z);
         // the sibling lies across the face when the normalised index is even;
         // siblings differ in the exit axis's octant bit only
         inner = __builtin_amdgcn_ubfe(Ex, lw, 1u) == 0u;
@@ -905,12 +908,13 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
       uint32_t Nn = neighbour(r);
       uint64_t null = lanes(Nn >= v.n_nodes);
       uint4 rn = pool.record(lane(null), Nn);
-      // certified when two planes exceed the threshold (the minimum's own test
-      // is always false, so this is the majority of the three)
-      const float thr = __builtin_fmaf(Smin, CERT_K, CERT_B * beta);
-      const uint64_t s0 = lanes(S.x > thr);
-      const uint64_t s1 = lanes(S.y > thr);
-      const uint64_t s2 = lanes(S.z > thr);
+      // certified when the lower bounds of the two other planes exceed the
+      // upper bound of the minimum (whose own test is always false, so this is
+      // the majority of the three)
+      const float up_min = Smin + ex;
+      const uint64_t s0 = lanes(S.x - eb.x > up_min);
+      const uint64_t s1 = lanes(S.y - eb.y > up_min);
+      const uint64_t s2 = lanes(S.z - eb.z > up_min);
       const uint64_t unsure = lanes(true) & ~((s0 & s1) | (s2 & (s0 | s1)));
       float Sx = Smin;  // exit plane value (the smallest one unless FP64 decides)
       if (unsure) {
@@ -951,7 +955,7 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
       bool cut = false;
       float Sl = Sx;  // where this leaf's segment ends
       if constexpr (SPLIT) {
-        const float eb_end = __builtin_fmaf(DESC_A, Sx, beta) + e_end;
+        const float eb_end = ex + e_end;
         if (Sx + eb_end >= s_end) {
           if (Sx - eb_end > s_end) {
             cut = true;
@@ -963,11 +967,9 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
         Sl = cut ? s_end : Sx;
       }
       const int nlw = (int)opaque(0u - lw);
-      // length precision guard (a uniform test but for refilled lanes)
-      if ((step & (GUARD_EVERY - 1u)) == GUARD_EVERY - 1u) {
-        asm volatile("");  // a branch, not selects
-        need64 = need64 || ldexpf(__builtin_fmaf(GUARD_A, Sx, 2.0f * beta), nlw) > GUARD_MAX;
-      }
+      // length precision guard: a new frame once the bound on this segment's
+      // length exceeds GUARD_MAX leaf edges
+      need64 = need64 || ldexpf(ex + e_ent, nlw) > GUARD_MAX;
       // composite; every visited leaf is recorded: for a ray outside the face
       // band the exact segment is positive even when it rounds to 0 here
       // (-log2(e) and the leaf's scale as one exact-scaled factor; kappa times
@@ -1006,6 +1008,7 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
       r = rn;
       pay = pool.payload(I);
       s_ent = Sx;
+      e_ent = ex;
       kbe = kbit;
       // one base cell on along the exit axis, then the low bits of the new
       // cell's width (a leaf's depth is in its record; a refined neighbour is
@@ -1020,19 +1023,17 @@ __device__ void cast_fp32(const DView& v, const RaySlot slot, const V3<double>& 
       // ---- refined cell: one level down, in the same iteration as the leaf
       // step that entered it
       const uint32_t half = 1u << (lw - 1u);
-      const float e_sum = __builtin_fmaf(DESC_A, s_ent, CERT_B * beta);
-      uint64_t far[3], sure = ~par_mask();
+      // (along the axis of the face that it was entered through, the mid-plane
+      // lies half a cell, far more than the bounds, past the entry)
+      uint64_t far[3], sure = lanes(lw > lw_min) & ~par_mask();
       V3<uint32_t> Em;
       for (int k = 0; k < 3; ++k) {
         set(Em, k, get(E, k) - half);  // the last base cell before the mid-plane
         const float Nf = (float)(int32_t)(get(Em, k) - get(E0, k));
         const float diff = s_ent - __builtin_fmaf(Nf, get(tD, k), get(S0, k));
-        const float G = __builtin_fmaf(__builtin_fabsf(Nf), get(tD, k), get(S0, k));
         far[k] = lanes(diff >= 0.0f);
-        sure &= lanes(__builtin_fabsf(diff) > __builtin_fmaf(DESC_A, G, e_sum));
+        sure &= lanes(__builtin_fabsf(diff) > e_ent + bound(Nf, k));
       }
-      // the frame must also be fine enough for the child
-      sure &= lanes(ldexpf(__builtin_fmaf(GUARD_A, s_ent, 2.0f * beta), 1 - (int)lw) <= GUARD_DESC);
       need64 = !lane(sure);
       if (!need64) {
         // octant bits: the far child is the upper one where the ray goes up
@@ -1883,11 +1884,11 @@ __device__ __forceinline__ void view_start(const DViewHost& v, DView& dst, uint3
   dst.start_c[0] = c.x;
   dst.start_c[1] = c.y;
   dst.start_c[2] = c.z;
+  const uint32_t lw = v.max_depth - dep;
   for (int k = 0; k < 3; ++k) {
     const double Q = ldexp(v.o[k], (int)v.max_depth);
-    dst.start_base[k] = get(C, k);
-    dst.start_up[k] = ((double)get(C, k) + 1.0) - Q;
-    dst.start_dn[k] = Q - (double)get(C, k);
+    dst.start_up[k] = (double)((get(c, k) + 1u) << lw) - Q;
+    dst.start_dn[k] = Q - (double)(get(c, k) << lw);
   }
   dst.start_ok = 1u;
 }

@@ -154,9 +154,8 @@ struct DViewHost {
 struct DView : DViewHost {
   uint32_t start_ok, start_node, start_dep;
   uint32_t start_c[3];     // the leaf's integer coordinates at start_dep
-  uint32_t start_base[3];  // the eye's cell at the deepest level
-  uint32_t pad;
-  double start_up[3], start_dn[3];  // from the eye to that cell's upper and lower planes, cells
+  double start_up[3], start_dn[3];  // from the eye to its upper and lower planes, in cells of the
+                                    // deepest level
 };
 
 // Work queues: the work items (tiles or 64-ray chunks) are split into
