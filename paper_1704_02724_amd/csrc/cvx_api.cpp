@@ -8,6 +8,7 @@
 #include <new>
 #include <string>
 #include <unordered_map>
+#include <unordered_set>
 #include <vector>
 
 #include "cvx_internal.h"
@@ -863,7 +864,11 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
   uint64_t n_cur = c.n_nodes;
   std::vector<uint32_t> touched;                   // nodes whose record word changes
   std::vector<std::pair<uint32_t, uint64_t>> paint;  // (node, payload index), in order
-  std::unordered_map<uint32_t, uint32_t> changed;   // refined or coarsened node -> depth
+  // refined or coarsened node -> depth, of the nodes from before the batch; what
+  // happens below a cell that the batch refined is covered by that cell, and
+  // the links stored for a node of a reused group are not its own
+  std::unordered_map<uint32_t, uint32_t> changed;
+  std::unordered_set<uint32_t> made;  // groups that the batch has given out
   auto set_x = [&](uint32_t i, uint32_t x) {
     undo.emplace_back(i, c.mirror[i]);
     c.mirror[i] = x;
@@ -915,9 +920,9 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
       for (uint32_t o = 0; o < 8; ++o) {
         set_x((uint32_t)g + o, 1u | ((d + 1) << 1));
         paint.emplace_back((uint32_t)g + o, ed.first_payload + o);
-        changed.erase((uint32_t)g + o);  // new children: covered by their parent
       }
-      changed[ed.node] = d;
+      if (!made.count(ed.node & ~7u)) changed[ed.node] = d;
+      made.insert((uint32_t)g);
       --c.leaves_at_depth[d];
       c.leaves_at_depth[d + 1] += 8;
       ++c.n_refined;
@@ -937,7 +942,7 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
         set_x(g + o, CVX_FREE);
         changed.erase(g + o);            // no longer in the tree
       }
-      changed[ed.node] = dc - 1;
+      if (!made.count(ed.node & ~7u)) changed[ed.node] = dc - 1;
       c.free_groups.push_back(g);
       c.leaves_at_depth[dc] -= 8;
       ++c.leaves_at_depth[dc - 1];
@@ -1074,6 +1079,7 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
     c.epoch = 0;
   }
   if (e != hipSuccess) return device_fail(e, where);
+  const uint32_t base = c.epoch + 1u;  // the mark of the first payload
   uint8_t* blk = (uint8_t*)(kept ? ctx->d_edit : b_blob.p);
   STEP(hipMemcpyAsync(blk, blob.data(), up_bytes, hipMemcpyHostToDevice, ctx->stream));
   const bool small = n_changed && n_changed <= kSmallChanged && n_paint <= kSmallPaints;
@@ -1109,7 +1115,7 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
     ea.n_paint = (uint32_t)n_paint;
     ea.n_changed = (uint32_t)n_changed;
     ea.words = lb / 8;
-    ea.base = c.epoch + 1u;
+    ea.base = base;
     ea.epoch = c.epoch + (uint32_t)n_paint + 1u;
     ea.R = R;
     ea.first_level = d_first;
@@ -1121,7 +1127,7 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
                                        (const uint32_t*)(blk + o_xs), n_touched, c.rec),
            "k_scatter_records");
     LAUNCH(cvx::launch_scatter_payloads(ctx->stream, (const uint32_t*)(blk + o_pids), blk + o_psrc,
-                                        n_paint, lb, c.pay, c.mark, c.epoch + 1u),
+                                        n_paint, lb, c.pay, c.mark, base),
            "k_scatter_payloads");
   }
   c.epoch += (uint32_t)n_paint;
@@ -1166,7 +1172,7 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
       LAUNCH(cvx::launch_dirty_roots(ctx->stream, (const uint32_t*)(blk + o_ch),
                                      (const uint32_t*)(blk + o_chd), n_changed, c.rec, R,
                                      (uint32_t*)(blk + o_roots), (uint32_t*)(blk + o_rootd), counts,
-                                     c.n_nodes),
+                                     c.n_nodes, c.mark, base),
              "k_dirty_roots");
     }
     for (bool again = true; e == hipSuccess && again && depth > level;) {

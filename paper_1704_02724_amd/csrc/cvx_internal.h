@@ -258,7 +258,7 @@ int launch_links(void* stream, uint32_t first_level, uint32_t last_level, void* 
                  uint32_t* mark, uint32_t epoch);
 int launch_dirty_roots(void* stream, const uint32_t* changed, const uint32_t* depth, uint64_t n,
                        const void* rec, uint32_t R, uint32_t* out, uint32_t* out_depth,
-                       uint32_t* out_count, uint64_t n_nodes);
+                       uint32_t* out_count, uint64_t n_nodes, uint32_t* mark, uint32_t base);
 // Words of the state of launch_pool_build: refined nodes found per level, then
 // a word that is not 0 when the pool is invalid; the list of refined nodes (as
 // many as there are child groups) follows at UP_LIST.

@@ -343,10 +343,18 @@ __global__ __launch_bounds__(256) void k_links_level(
 // a changed node that is refined (its children are new), or a refined
 // same-depth face neighbour of a changed node (a sibling, a same-depth outer
 // link, or at depth 0 a neighbouring root).  Outer links to coarser cells
-// are leaves and have nothing below them.
+// are leaves and have nothing below them (one that the batch refined is a
+// changed node itself, at its own, smaller depth).
+// The links are from before the batch.  One may name a node whose group the
+// batch has freed and given out again, now at any depth: rebuilt at this one
+// and marked, it would be passed over at its own.  Every child that a batch
+// creates is painted by it, so it carries a mark of `base` or above; a refined
+// neighbour with such a mark is left out, being either below a refined cell
+// that is listed or a changed node, listed for itself.
 __device__ __forceinline__ void dirty_roots_of(uint32_t X, uint32_t d, const uint4* rec, uint32_t R,
                                                uint32_t* out, uint32_t* out_depth,
-                                               uint32_t* out_count, uint64_t n_nodes) {
+                                               uint32_t* out_count, uint64_t n_nodes,
+                                               uint32_t* mark, uint32_t base) {
   uint32_t cand[7];
   cand[0] = X;
   if (d == 0) {
@@ -368,6 +376,8 @@ __device__ __forceinline__ void dirty_roots_of(uint32_t X, uint32_t d, const uin
     if (N == CVX_NONE || (uint64_t)N >= n_nodes) continue;
     const uint32_t x = rec[N].x;
     if (is_leaf(x)) continue;  // or not in the tree (CVX_FREE)
+    if (j && __hip_atomic_load(&mark[N], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= base)
+      continue;
     const uint32_t slot = atomicAdd(out_count, 1u);
     out[slot] = N;
     out_depth[slot] = d;
@@ -378,10 +388,11 @@ __global__ void k_dirty_roots(const uint32_t* __restrict__ changed,
                               const uint32_t* __restrict__ depth, uint64_t n,
                               const uint4* __restrict__ rec, uint32_t R,
                               uint32_t* __restrict__ out, uint32_t* __restrict__ out_depth,
-                              uint32_t* __restrict__ out_count, uint64_t n_nodes) {
+                              uint32_t* __restrict__ out_count, uint64_t n_nodes,
+                              uint32_t* __restrict__ mark, uint32_t base) {
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  dirty_roots_of(changed[i], depth[i], rec, R, out, out_depth, out_count, n_nodes);
+  dirty_roots_of(changed[i], depth[i], rec, R, out, out_depth, out_count, n_nodes, mark, base);
 }
 
 // A small batch in one launch, by one workgroup: records, payloads, region
@@ -417,7 +428,7 @@ __global__ __launch_bounds__(1024) void k_edit_small(EditArgs a) {
   }
   for (uint32_t i = t; i < a.n_changed; i += nt)
     dirty_roots_of(a.changed[i], a.changed_depth[i], rec, a.R, a.roots, a.root_depth, &n_roots,
-                   a.n_nodes);
+                   a.n_nodes, a.mark, a.base);
   __syncthreads();
   const uint32_t n_r = n_roots, o = t & 7u;
   if (t == 0) a.counts[0] = n_r;
@@ -467,12 +478,12 @@ int launch_edit_small(void* stream, const EditArgs& a) {
 
 int launch_dirty_roots(void* stream, const uint32_t* changed, const uint32_t* depth, uint64_t n,
                        const void* rec, uint32_t R, uint32_t* out, uint32_t* out_depth,
-                       uint32_t* out_count, uint64_t n_nodes) {
+                       uint32_t* out_count, uint64_t n_nodes, uint32_t* mark, uint32_t base) {
   if (!n) return hipSuccess;
   const uint32_t bs = 256;
   hipLaunchKernelGGL(k_dirty_roots, dim3((uint32_t)((n + bs - 1) / bs)), dim3(bs), 0,
                      (hipStream_t)stream, changed, depth, n, (const uint4*)rec, R, out, out_depth,
-                     out_count, n_nodes);
+                     out_count, n_nodes, mark, base);
   return (int)hipGetLastError();
 }
 
