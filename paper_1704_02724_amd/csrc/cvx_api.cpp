@@ -21,6 +21,7 @@ using cvx::DView;
 struct GraphKey {
   uint32_t variant = ~0u, tw = 0, th = 0, wgs = 0, wg = 0, item_tiles = 1, refill_min = 0,
            pieces = 1;
+  uint32_t merge_views = 0;  // grid of the merge of chord pieces (0: none)
   bool trace = false, stats = false, out64 = false, small = false, per_ray_start = false,
        by_args = false, root_leaves = false;
   const void* out = nullptr;
@@ -30,6 +31,7 @@ struct GraphKey {
   bool operator==(const GraphKey& o) const {
     return variant == o.variant && tw == o.tw && th == o.th && wgs == o.wgs && wg == o.wg &&
            item_tiles == o.item_tiles && refill_min == o.refill_min && pieces == o.pieces &&
+           merge_views == o.merge_views &&
            split_tmp == o.split_tmp &&
            trace == o.trace && stats == o.stats && out64 == o.out64 && small == o.small &&
            per_ray_start == o.per_ray_start && by_args == o.by_args &&
@@ -647,6 +649,7 @@ int render_launch(cvx_ctx* ctx, const cvx_view* views, int n_views, void* out_de
   key.item_tiles = p.item_tiles;
   key.refill_min = p.refill_min;
   key.pieces = p.pieces;
+  key.merge_views = merge ? (uint32_t)n_views : 0u;
   key.split_tmp = a.split_tmp;
   key.trace = false;
   key.stats = stats;
