@@ -1068,20 +1068,20 @@ int edit_impl(cvx_ctx* ctx, DevCanvas& c, const cvx_edit* edits, uint32_t n_edit
     kept = false;
   }
   if (!kept) STEP(hipMalloc(&b_blob.p, std::max<uint64_t>(at, 16)));
-  if (e == hipSuccess && c.mark_cap < c.n_nodes) {
-    // marks, grown with the pool
+  const bool grow = c.mark_cap < c.n_nodes;  // marks, grown with the pool
+  const bool again = cvx::count_again(c.epoch, n_paint, grow);
+  if (e == hipSuccess && grow) {
     if (c.mark) (void)hipFree(c.mark);
     c.mark = nullptr;
     c.mark_cap = 0;
     STEP(hipMalloc((void**)&c.mark, c.cap_nodes * 4));
     STEP(hipMemsetAsync(c.mark, 0, c.cap_nodes * 4, ctx->stream));
     if (e == hipSuccess) c.mark_cap = c.cap_nodes;
-  } else if (e == hipSuccess && c.epoch > 0xffffffffu - n_paint - 64u) {
-    // the running count starts again
+  } else if (e == hipSuccess && again) {
     STEP(hipMemsetAsync(c.mark, 0, c.mark_cap * 4, ctx->stream));
-    c.epoch = 0;
   }
   if (e != hipSuccess) return device_fail(e, where);
+  if (again) c.epoch = 0;
   const uint32_t base = c.epoch + 1u;  // the mark of the first payload
   uint8_t* blk = (uint8_t*)(kept ? ctx->d_edit : b_blob.p);
   STEP(hipMemcpyAsync(blk, blob.data(), up_bytes, hipMemcpyHostToDevice, ctx->stream));

@@ -117,6 +117,16 @@ struct DevCanvas {
   StrokeState stroke;
 };
 
+// Numbers of a batch's link rebuild and of its repetitions with larger lists (at
+// most one per power of two).
+constexpr uint32_t kLinkRuns = 64;
+// Whether the running count of a pool's marks starts again from 0 for a batch of
+// n_paint payloads: where it would pass 32 bits, and wherever the marks are
+// new (and all 0).
+inline bool count_again(uint32_t epoch, uint64_t n_paint, bool new_marks) {
+  return new_marks || epoch + n_paint + kLinkRuns > 0xffffffffull;
+}
+
 // Depth of the top-level table of a canvas: at most 6 levels and 2^18 cells,
 // never below the deepest level present; 0 means no table.
 inline uint32_t top_table_depth(uint32_t R, uint32_t depth) {
