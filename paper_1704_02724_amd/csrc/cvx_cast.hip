@@ -140,10 +140,12 @@ __device__ __forceinline__ double rsq_nr(double x) {
   for (int i = 0; i < 2; ++i) y = __builtin_fma(y, __builtin_fma(-h * y, y, 0.5), y);
   return y;
 }
+// (below this the reciprocal is taken as infinite)
+constexpr double kParallel64 = 0x1p-1000;
 __device__ __forceinline__ double rcp_nr(double x) {
   double r = __builtin_amdgcn_rcp(x);
   for (int i = 0; i < 2; ++i) r = __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
-  return __builtin_fabs(x) < 0x1p-1000 ? __builtin_copysign(__builtin_inf(), x) : r;
+  return __builtin_fabs(x) < kParallel64 ? __builtin_copysign(__builtin_inf(), x) : r;
 }
 
 // The same without the inf: NaN for |x| < 2^-1022 or so.
@@ -1123,8 +1125,9 @@ __device__ void cast_fp64(const DView& v, const V3<double>& d, const V3<double>&
     double qk = ok + en.t0 * dk;
     if (k == en.kin) qk = en.side ? Rd : 0.0;
     set(q, k, qk < 0.0 ? 0.0 : (qk > Rd ? Rd : qk));
-    // a ray parallel to the axis never reaches its planes: t = inf
-    const bool par = dk == 0.0;
+    // a ray parallel to the axis (as far as rcp_nr can tell) never reaches its
+    // planes: t = inf
+    const bool par = __builtin_fabs(dk) < kParallel64;
     set(os, k, par ? -__builtin_inf() : ldexp(get(up, k) ? ok : -ok, (int)D));
     set(is, k, par ? 1.0 : ldexp(__builtin_fabs(get(inv, k)), -(int)D));
     upm[k] = lanes(get(up, k));
@@ -1224,7 +1227,7 @@ __device__ void cast_fp64(const DView& v, const V3<double>& d, const V3<double>&
         const V3<double> o{v.o[0], v.o[1], v.o[2]};
         const V3<uint32_t> n = flip(deep_coords(o, up, v.R, D), up);
         for (int k = 0; k < 3; ++k) {
-          const uint64_t pk = lanes(get(d, k) == 0.0);
+          const uint64_t pk = lanes(__builtin_fabs(get(d, k)) < kParallel64);
           far[k] = (far[k] & ~pk) | (lanes((int32_t)get(n, k) > (int32_t)get(Em, k)) & pk);
         }
       }
