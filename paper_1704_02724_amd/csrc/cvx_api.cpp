@@ -201,11 +201,7 @@ int cvx_create(cvx_ctx** out, int hip_device, void* hip_stream) {
 void cvx_destroy(cvx_ctx* ctx) {
   if (!ctx) return;
   (void)hipSetDevice(ctx->device);
-  // (a stream the caller has destroyed since: wait for the device instead)
-  if (hipStreamSynchronize(ctx->stream) != hipSuccess) {
-    (void)hipGetLastError();
-    (void)hipDeviceSynchronize();
-  }
+  (void)hipStreamSynchronize(ctx->stream);
   drop_graph(ctx);
   for (auto& c : ctx->canvases) free_canvas(c);
   if (ctx->d_stage) (void)hipFree(ctx->d_stage);
@@ -234,12 +230,8 @@ int cvx_set_stream(cvx_ctx* ctx, void* hip_stream) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (to) CVX_HIP(hipStreamIsCapturing(to, &cap));
   if (cap == hipStreamCaptureStatusNone) {
-    hipError_t e = hipEventRecord(ctx->moved, ctx->stream);
-    if (e == hipSuccess) e = hipStreamWaitEvent(to, ctx->moved, 0);
-    if (e != hipSuccess) {  // the old stream was destroyed
-      (void)hipGetLastError();
-      CVX_HIP(hipDeviceSynchronize());
-    }
+    CVX_HIP(hipEventRecord(ctx->moved, ctx->stream));
+    CVX_HIP(hipStreamWaitEvent(to, ctx->moved, 0));
   }
   ctx->stream = to;
   return CVX_OK;

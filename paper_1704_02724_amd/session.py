@@ -21,11 +21,13 @@ class Session:
         torch.cuda.set_device(device)
         self.device = torch.device("cuda", device)
         # a stream of our own (default priority): graph capture needs a
-        # non-null stream.  Renders go to torch's current stream: through a
-        # stream of their own, ordered against it by two events, every frame
-        # cost about 20 us more (a 64x64 view: 95 us against 72)
+        # non-null stream, and uploads, edits and strokes run there.  Renders go
+        # to torch's current stream: through a stream of their own, ordered
+        # against it by two events, every frame cost about 20 us more (a 64x64
+        # view: 95 us against 72)
         self._home = torch.cuda.Stream(self.device)
         self._bound = self._home
+        self._external = None
         self.ctx = cvx.cvx_create(device, self._home.cuda_stream)
         self.descs = {}
 
@@ -44,27 +46,32 @@ class Session:
     def upload(self, canvas_id, canvas):
         d = cvx.make_desc(canvas.origin, canvas.root_edge, canvas.R, canvas.max_depth,
                           canvas.leaf_format)
+        self._bind(self._home)
         cvx.cvx_upload_pool(self.ctx, canvas_id, d, canvas.nodes, canvas.leaves)
         self.descs[canvas_id] = d
 
     def edit(self, canvas_id, edits, payloads):
         """Apply pool edits (cvx_edit_pool); returns the first child id per edit."""
         self.torch.cuda.current_stream(self.device).synchronize()
+        self._bind(self._home)
         return cvx.cvx_edit_pool(self.ctx, canvas_id, edits, payloads)
 
     def stroke_begin(self, canvas_id, stamps, rgb, sigma, radius, k_refine, coarsen=False):
         """Paint a brush stroke into the existing leaves (cvx_stroke_begin);
         returns the number of leaves waiting for a split."""
         self.torch.cuda.current_stream(self.device).synchronize()
+        self._bind(self._home)
         return cvx.cvx_stroke_begin(self.ctx, canvas_id, stamps, rgb, sigma, radius, k_refine,
                                     coarsen)
 
     def stroke_step(self, canvas_id):
         """One deferred refinement level of the stroke (cvx_stroke_step)."""
         self.torch.cuda.current_stream(self.device).synchronize()
+        self._bind(self._home)
         return cvx.cvx_stroke_step(self.ctx, canvas_id)
 
     def free(self, canvas_id):
+        self._bind(self._home)
         cvx.cvx_free_pool(self.ctx, canvas_id)
         self.descs.pop(canvas_id, None)
 
@@ -76,13 +83,31 @@ class Session:
             self._home.wait_stream(self._bound)
         return self._home
 
+    def _bind(self, stream):
+        """The context's next calls on `stream`, after those so far.  The context
+        goes back to a stream when it leaves it, so this is one of torch's own,
+        which stay for the life of the process."""
+        if stream != self._bound:
+            cvx.cvx_set_stream(self.ctx, stream.cuda_stream)
+            self._bound = stream
+
     def _enter(self):
+        """Binds the current stream, or, where that is someone else's (an
+        ExternalStream, whose id is its handle) and may be destroyed at any time
+        after this call, the session's own between two waits."""
         cur = self.torch.cuda.current_stream(self.device)
-        if cur != self._bound:
-            cvx.cvx_set_stream(self.ctx, cur.cuda_stream)
-            self._bound = cur
+        if cur.cuda_stream and cur.stream_id == cur.cuda_stream:
+            self._bind(self._home)
+            self._home.wait_stream(cur)
+            self._external = cur
+        else:
+            self._bind(cur)
+            self._external = None
 
     def _leave(self, *tensors):
+        if self._external is not None:
+            self._external.wait_stream(self._home)
+            self._external = None
         for t in tensors:  # one allocated on another stream lives until the render is done
             t.record_stream(self._bound)
 

@@ -1,0 +1,68 @@
+"""Uploads, edits and strokes do not go to the stream of the last render, which
+its owner may have destroyed."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from canvasgen import LEAF_RGBA8_F16, make_view, trees
+from canvasgen.pool import LEAF_DTYPE
+
+from editmodel import PAINT
+
+pytestmark = pytest.mark.gpu
+
+VIEW = [make_view((0.4, 0.5, -0.5), (0.0, 0.05, 1.0), 0.5, 96, 80)]
+
+
+@pytest.fixture
+def sess():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1704_02724_amd.session import Session
+    with Session(0) as s:
+        s.cv = trees.random_tree(1, 6, seed=51, max_nodes=4000, leaf_format=LEAF_RGBA8_F16)
+        s.upload(0, s.cv)
+        yield s
+
+
+def _render_on_a_stream_that_goes(sess):
+    from paper_1704_02724_amd import cvx
+    hip, torch = cvx.library(), sess.torch   # the library's own HIP runtime
+    h = ctypes.c_void_p()
+    assert hip.hipStreamCreate(ctypes.byref(h)) == 0
+    ext = torch.cuda.ExternalStream(h.value, device=sess.device)
+    with torch.cuda.stream(ext):
+        img = sess.render(VIEW).cpu().numpy()
+    ext.synchronize()
+    assert hip.hipStreamDestroy(h) == 0
+    return img
+
+
+@pytest.mark.parametrize("what", ["edit", "upload", "stroke", "free", "read", "render", "close"])
+def test_after_the_renders_stream_is_gone(sess, what):
+    from paper_1704_02724_amd import cvx
+    ref = sess.render(VIEW).cpu().numpy()
+    records = cvx.cvx_read_records(sess.ctx, 0)
+    np.testing.assert_array_equal(_render_on_a_stream_that_goes(sess), ref)
+    if what == "edit":
+        leaf = int(np.nonzero(sess.cv.nodes[8:, 0] >= 0x80000000)[0][0]) + 8
+        sess.edit(0, [(PAINT, leaf, 0)],
+                  sess.cv.leaves[sess.cv.nodes[leaf, 0] & 0x7FFFFFFF].reshape(1))
+    elif what == "upload":
+        sess.upload(0, sess.cv)
+    elif what == "stroke":
+        n = sess.stroke_begin(0, np.array([[0.5, 0.5, 0.5, 0.05]]), (1.0, 0.0, 0.0), 0.0, 0.05, 2.0)
+        while n:
+            n = sess.stroke_step(0)
+        sess.upload(0, sess.cv)
+    elif what == "free":
+        sess.free(0)
+        sess.upload(0, sess.cv)
+    elif what == "read":
+        np.testing.assert_array_equal(cvx.cvx_read_records(sess.ctx, 0), records)
+        leaves = cvx.cvx_read_payloads(sess.ctx, 0, LEAF_DTYPE[LEAF_RGBA8_F16])
+        assert len(leaves) == len(records)
+    if what != "close":
+        np.testing.assert_array_equal(sess.render(VIEW).cpu().numpy(), ref)
