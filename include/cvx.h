@@ -220,8 +220,9 @@ int cvx_create(cvx_ctx** ctx, int hip_device, void* hip_stream);
 
 /* Enqueue the context's further calls on hip_stream (borrowed; NULL = the null
  * stream) instead of the stream it was on, after what it enqueued there (no
- * wait is inserted when hip_stream is being captured).  It has to stay valid
- * until another one is set or the context is destroyed.  A caller that renders
+ * wait is inserted when hip_stream is being captured and the other is not; the
+ * other way round the call fails).  It has to stay valid until another one is set
+ * or the context is destroyed.  A caller that renders
  * on the stream its other work is on needs no events between the two, which
  * cost about 20 us a frame.  Graphs (use_graph) stay available as the stream
  * given to cvx_create had it. */

@@ -111,6 +111,14 @@ void drop_graph(cvx_ctx* ctx) {
   ctx->gkey = GraphKey();
 }
 
+// Whether a stream is being captured, and by which capture.
+hipError_t capture_of(hipStream_t s, bool& captured, unsigned long long& id) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  const hipError_t e = s ? hipStreamGetCaptureInfo(s, &st, &id) : hipSuccess;
+  captured = e == hipSuccess && st != hipStreamCaptureStatusNone;
+  return e;
+}
+
 uint32_t leaf_bytes(uint32_t fmt) { return fmt == CVX_LEAF_F64 ? 32u : 8u; }
 
 }  // namespace
@@ -224,12 +232,18 @@ int cvx_set_stream(cvx_ctx* ctx, void* hip_stream) {
   const hipStream_t to = (hipStream_t)hip_stream;
   if (to == ctx->stream) return CVX_OK;
   CVX_HIP(hipSetDevice(ctx->device));
-  // what the context enqueued on the old stream comes first.  A stream being
-  // captured cannot wait for work outside its capture: there the caller has
-  // synchronised before.
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (to) CVX_HIP(hipStreamIsCapturing(to, &cap));
-  if (cap == hipStreamCaptureStatusNone) {
+  // what the context enqueued on the old stream comes first, in a capture of
+  // both streams too (the calls share the context's view table and queues).  A
+  // stream being captured cannot wait for work outside its capture: there the
+  // caller has synchronised before.
+  bool to_captured = false, captured = false;
+  unsigned long long to_id = 0, id = 0;
+  CVX_HIP(capture_of(to, to_captured, to_id));
+  CVX_HIP(capture_of(ctx->stream, captured, id));
+  if (captured && !(to_captured && to_id == id))
+    return fail(ctx, CVX_ERR_INVALID_ARG,
+                "the context's stream is being captured, and the new one not in that capture");
+  if (captured == to_captured) {
     CVX_HIP(hipEventRecord(ctx->moved, ctx->stream));
     CVX_HIP(hipStreamWaitEvent(to, ctx->moved, 0));
   }

@@ -1,5 +1,6 @@
-"""Uploads, edits and strokes do not go to the stream of the last render, which
-its owner may have destroyed."""
+"""Streams that are gone or captured: uploads, edits and strokes do not go to the
+stream of the last render, which its owner may have destroyed, and renders
+captured on several streams of one capture follow one another."""
 import ctypes
 
 import numpy as np
@@ -66,3 +67,40 @@ def test_after_the_renders_stream_is_gone(sess, what):
         assert len(leaves) == len(records)
     if what != "close":
         np.testing.assert_array_equal(sess.render(VIEW).cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_renders_on_the_streams_of_one_capture(sess, noalloc):
+    """Two streams forked before either render: only the context orders them."""
+    torch = sess.torch
+    small = [make_view((0.45, 0.55, 0.5), (1.0, 0.1, 0.2), 0.8, 50, 33)]
+    jobs = [VIEW, small, VIEW, small]
+    ref = [sess.render(v, noalloc=noalloc).clone() for v in jobs]
+    out = [torch.empty_like(r) for r in ref]
+    streams = [torch.cuda.Stream(sess.device) for _ in jobs]
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        cur = torch.cuda.current_stream(sess.device)
+        for st in streams:
+            st.wait_stream(cur)
+        for st, v, o in zip(streams, jobs, out):
+            with torch.cuda.stream(st):
+                sess.render(v, out=o, noalloc=noalloc)
+        for st in streams:
+            cur.wait_stream(st)
+    for _ in range(4):
+        for o in out:
+            o.fill_(-1.0)
+        g.replay()
+        torch.cuda.synchronize()
+        for o, r in zip(out, ref):
+            assert torch.equal(o, r)
+        assert torch.equal(sess.render(VIEW), ref[0])   # eager work between the replays
+    with pytest.raises(Exception, match="captured"):
+        other = torch.cuda.Stream(sess.device)
+        with torch.cuda.graph(torch.cuda.CUDAGraph(), capture_error_mode="thread_local"):
+            sess.render(VIEW, out=out[0], noalloc=noalloc)
+            with torch.cuda.stream(other):
+                sess.render(VIEW, out=out[0], noalloc=noalloc)
+    assert torch.equal(sess.render(VIEW), ref[0])
