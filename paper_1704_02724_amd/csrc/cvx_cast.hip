@@ -39,7 +39,7 @@
 #define CVX_CAST64_WAVES 6
 #endif
 #ifndef CVX_CAST32R_WAVES
-#define CVX_CAST32R_WAVES 7
+#define CVX_CAST32R_WAVES 5
 #endif
 
 namespace cvx {
@@ -1844,8 +1844,12 @@ __global__ void k_merge_pieces(const DView* views, const CastHeader* hdr, const 
   }
 }
 
-// The refilling render keeps the ray setup inside its loop; seven
-// wavefronts per SIMD leave it the registers to do so without spills.
+// The refilling render keeps the ray set-up inside its loop, next to the state
+// of the lanes that keep running: at five wavefronts per SIMD it spills 24 bytes
+// per lane, at seven 144, at four none.  Best of 24 launch shapes with 7 / 6 / 5 /
+// 4, in us: depth-24 stereo 1867 / 1836 / 1858 / 1981, zoomed depth-30 1692 /
+// 1636 / 1610 / 1746, 64 views 2211 / 2123 / 2143 / 2295, 64x64 141 / 135 / 125 /
+// 127 (one ray per lane: 691, 529, 864, 72).
 template <bool SMALL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CVX_CAST32R_WAVES))) void k_cast32r(
     CastArgs a) {
