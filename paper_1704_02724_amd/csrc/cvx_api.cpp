@@ -1314,6 +1314,12 @@ constexpr uint64_t kWalkCells = 1u << 16;
 constexpr uint32_t kWalkLevels = 8;       // levels between two read-backs at most
 constexpr uint32_t kWalkHead = 64;        // bytes: pending count, then a count per level
 constexpr uint64_t kWalkFirst = 512;      // pending entries that come with the counts
+constexpr uint64_t kWalkRead = kWalkHead + kWalkFirst * sizeof(cvx::StrokePend);
+// the counts, the pending list and the two frontier lists, as much as is read back at least
+constexpr uint64_t walk_bytes(uint64_t cap) {
+  return std::max<uint64_t>(
+      kWalkHead + cap * (sizeof(cvx::StrokePend) + 2 * sizeof(cvx::StrokeItem)), kWalkRead);
+}
 
 // One walk of the stroke from a frontier (nullptr: the root array) down to
 // the leaves on the GPU; the leaves still waiting for a split are appended to
@@ -1343,31 +1349,35 @@ int stroke_walk(cvx_ctx* ctx, DevCanvas& c, const std::vector<cvx::StrokeItem>* 
   STEP(hipMemcpyAsync(b_in.p, blob.data(), blob.size(), hipMemcpyHostToDevice, ctx->stream));
   const cvx::StrokeItem* items =
       start ? (const cvx::StrokeItem*)((uint8_t*)b_in.p + o_start) : nullptr;
-  std::vector<uint8_t> got(kWalkHead + kWalkFirst * sizeof(cvx::StrokePend));
+  std::vector<uint8_t> got(kWalkRead);
   for (uint32_t turn = 0; e == hipSuccess && n; ++turn) {
     if (n > 0x1fffffffull) { e = hipErrorUnknown; where = "stroke frontier too large"; break; }
     // levels that surely fit; a frontier too large for one gets its own lists
     uint32_t levels = 0;
     for (uint64_t m = n * 8; levels < kWalkLevels && m <= kWalkCells; m *= 8) ++levels;
+    // (or where the device has no room for the kept ones)
+    for (void*& p : ctx->d_walk)
+      if (levels && !p && hipMalloc(&p, walk_bytes(kWalkCells)) != hipSuccess) {
+        (void)hipGetLastError();
+        p = nullptr;
+        levels = 0;
+      }
+    const bool kept = levels != 0;
     uint64_t cap = kWalkCells;
-    if (!levels) {
+    if (!kept) {
       levels = 1;
       cap = 8 * n;
     }
     // a block of [head | pending | two lists]; turns alternate between two, so
     // that the frontier a turn starts from is not one it writes
-    const uint64_t bytes = kWalkHead + cap * sizeof(cvx::StrokePend) +
-                           2 * cap * sizeof(cvx::StrokeItem);
     uint8_t* blk = nullptr;
-    if (cap == kWalkCells) {
-      for (int k = 0; k < 2 && e == hipSuccess; ++k)
-        if (!ctx->d_walk[k]) STEP(hipMalloc(&ctx->d_walk[k], bytes));
+    if (kept) {
       blk = (uint8_t*)ctx->d_walk[turn & 1u];
     } else {
       DevBuf& own = b_own[turn & 1u];
       if (own.p) (void)hipFree(own.p);
       own.p = nullptr;
-      STEP(hipMalloc(&own.p, bytes));
+      STEP(hipMalloc(&own.p, walk_bytes(cap)));
       blk = (uint8_t*)own.p;
     }
     if (e != hipSuccess) break;
