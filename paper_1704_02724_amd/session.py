@@ -27,7 +27,8 @@ class Session:
         # view: 95 us against 72)
         self._home = torch.cuda.Stream(self.device)
         self._bound = self._home
-        self._external = None
+        self._around = None
+        self._taken = False
         self.ctx = cvx.cvx_create(device, self._home.cuda_stream)
         self.descs = {}
 
@@ -78,7 +79,9 @@ class Session:
     # -- stream ordering ----------------------------------------------------
     @property
     def stream(self):
-        """The session's own stream, ordered after every render so far."""
+        """The session's own stream.  Once a caller has it, renders go there, or
+        between two waits for it, in order with what the caller puts on it."""
+        self._taken = True
         if self._bound != self._home:
             self._home.wait_stream(self._bound)
         return self._home
@@ -92,22 +95,21 @@ class Session:
             self._bound = stream
 
     def _enter(self):
-        """Binds the current stream, or, where that is someone else's (an
-        ExternalStream, whose id is its handle) and may be destroyed at any time
-        after this call, the session's own between two waits."""
+        """Binds the current stream, or the session's own between two waits:
+        where a caller may have work on that one, and where the current one is
+        someone else's (an ExternalStream, whose id is its handle) and may be
+        destroyed at any time after this call."""
         cur = self.torch.cuda.current_stream(self.device)
-        if cur.cuda_stream and cur.stream_id == cur.cuda_stream:
-            self._bind(self._home)
+        external = cur.cuda_stream and cur.stream_id == cur.cuda_stream
+        self._around = cur if cur != self._home and (external or self._taken) else None
+        self._bind(cur if self._around is None else self._home)
+        if self._around is not None:
             self._home.wait_stream(cur)
-            self._external = cur
-        else:
-            self._bind(cur)
-            self._external = None
 
     def _leave(self, *tensors):
-        if self._external is not None:
-            self._external.wait_stream(self._home)
-            self._external = None
+        if self._around is not None:
+            self._around.wait_stream(self._home)
+            self._around = None
         for t in tensors:  # one allocated on another stream lives until the render is done
             t.record_stream(self._bound)
 

@@ -1,6 +1,7 @@
-"""Streams that are gone or captured: uploads, edits and strokes do not go to the
-stream of the last render, which its owner may have destroyed, and renders
-captured on several streams of one capture follow one another."""
+"""Streams that are gone, shared or captured: uploads, edits and strokes do not
+go to the stream of the last render, which its owner may have destroyed, renders
+are in order with a caller's work on the session's stream, and renders captured
+on several streams of one capture follow one another."""
 import ctypes
 
 import numpy as np
@@ -67,6 +68,28 @@ def test_after_the_renders_stream_is_gone(sess, what):
         assert len(leaves) == len(records)
     if what != "close":
         np.testing.assert_array_equal(sess.render(VIEW).cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(use_graph=True)])
+def test_work_on_the_sessions_stream(sess, kw):
+    """A copy of a frame on the session's stream, kept by the caller, comes after
+    that frame and before the next one overwrites it."""
+    torch = sess.torch
+    other = [make_view((0.45, 0.55, 0.5), (1.0, 0.1, 0.2), 0.8, 96, 80)]
+    ref = [sess.render(v).clone() for v in (VIEW, other)]
+    out = torch.empty_like(ref[0])
+    busy = torch.ones((2048, 2048), device=sess.device)
+    own = sess.stream
+    got = []
+    for i in range(6):
+        sess.render((VIEW, other)[i % 2], out=out, **kw)
+        with torch.cuda.stream(own):
+            for _ in range(4):
+                busy @ busy
+            got.append(out.clone())
+    torch.cuda.synchronize()
+    for i, g in enumerate(got):
+        assert torch.equal(g, ref[i % 2])
 
 
 @pytest.mark.parametrize("noalloc", [False, True])
