@@ -21,10 +21,10 @@ class Session:
         torch.cuda.set_device(device)
         self.device = torch.device("cuda", device)
         # a stream of our own (default priority): graph capture needs a
-        # non-null stream, and uploads, edits and strokes run there.  Renders go
-        # to torch's current stream: through a stream of their own, ordered
-        # against it by two events, every frame cost about 20 us more (a 64x64
-        # view: 95 us against 72)
+        # non-null stream.  Renders go to torch's current stream: through a
+        # stream of their own, ordered against it by two events, every frame
+        # cost about 20 us more (a 64x64 view: 95 us against 72).  Other calls
+        # follow on the stream of the last render (a change costs about 20 us)
         self._home = torch.cuda.Stream(self.device)
         self._bound = self._home
         self._around = None
@@ -47,32 +47,27 @@ class Session:
     def upload(self, canvas_id, canvas):
         d = cvx.make_desc(canvas.origin, canvas.root_edge, canvas.R, canvas.max_depth,
                           canvas.leaf_format)
-        self._bind(self._home)
         cvx.cvx_upload_pool(self.ctx, canvas_id, d, canvas.nodes, canvas.leaves)
         self.descs[canvas_id] = d
 
     def edit(self, canvas_id, edits, payloads):
         """Apply pool edits (cvx_edit_pool); returns the first child id per edit."""
         self.torch.cuda.current_stream(self.device).synchronize()
-        self._bind(self._home)
         return cvx.cvx_edit_pool(self.ctx, canvas_id, edits, payloads)
 
     def stroke_begin(self, canvas_id, stamps, rgb, sigma, radius, k_refine, coarsen=False):
         """Paint a brush stroke into the existing leaves (cvx_stroke_begin);
         returns the number of leaves waiting for a split."""
         self.torch.cuda.current_stream(self.device).synchronize()
-        self._bind(self._home)
         return cvx.cvx_stroke_begin(self.ctx, canvas_id, stamps, rgb, sigma, radius, k_refine,
                                     coarsen)
 
     def stroke_step(self, canvas_id):
         """One deferred refinement level of the stroke (cvx_stroke_step)."""
         self.torch.cuda.current_stream(self.device).synchronize()
-        self._bind(self._home)
         return cvx.cvx_stroke_step(self.ctx, canvas_id)
 
     def free(self, canvas_id):
-        self._bind(self._home)
         cvx.cvx_free_pool(self.ctx, canvas_id)
         self.descs.pop(canvas_id, None)
 
