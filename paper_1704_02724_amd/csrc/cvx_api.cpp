@@ -594,8 +594,8 @@ int render_launch(cvx_ctx* ctx, const cvx_view* views, int n_views, void* out_de
     a.end_point = tr->end_point;
   }
   // Workgroups of one wavefront while every CU has few (its own LDS and L1
-  // share): a 333x217 view measured 97 us in the kernel against 105 with four,
-  // 128x128 90 / 99, 64x64 71 / 74; with a full machine they are even.
+  // share): a 333x217 view measured 109 us in the kernel against 117 with four,
+  // 128x128 68 / 71, 64x64 71 / 74; with a full machine they are even.
   const uint32_t wg = p.wg ? p.wg : (H.total_work <= 8ull * ctx->n_cu ? 64u : 256u);
   // no more workgroups than there are work items for, to the next power of two
   // (a captured graph then serves view sets of about the same size)

@@ -558,8 +558,8 @@ struct LeafLoad<true> {
 // the FP32 rounding of the comparison (G >= |value|), folded into one fma
 constexpr float CERT_A = 0x1p-21f * 1.0625f + 0x1p-23f;
 constexpr float CERT_B = 1.0625f;
-constexpr uint32_t FRAME_LEVELS = 8;
-constexpr float GUARD_MAX = 0x1p-10f;
+constexpr uint32_t FRAME_LEVELS = 8;   // descents below a frame's first leaf
+constexpr float GUARD_MAX = 0x1p-10f;  // error of a segment's length, in leaf edges
 
 // Per-lane LDS slot holding the FP64 direction and reciprocal direction of the
 // lane's ray, [6][blockDim.x] doubles (component-major, so lanes read
@@ -609,8 +609,8 @@ struct RefillJob {
 // point.  shared_start: the ray starts in the view's shared eye leaf (en.t0 = 0
 // then, and the rest of en is not read).
 // ROOTS = false: no view has a leaf of depth 0 (one root, refined), so the step
-// needs no test for it: one compare and a branch over the root-array code, 4 %
-// of a depth-24 or depth-30 view (836 / 801 us, 577 / 554) and 8 us of a 64x64
+// needs no test for it: one compare and a branch over the root-array code, 4-6 %
+// of a depth-24 or depth-30 view (709 / 667 us, 527 / 505) and 6 us of a 64x64
 // view, where each branch of a lone wavefront's iteration is latency.
 template <bool TRACE, bool STATS, bool SMALL, bool REFILL = false, bool SPLIT = false,
           bool ROOTS = true>
