@@ -183,9 +183,9 @@ def time_variant(sess, views, variant, steps, warmup, tuning):
           for _ in range(steps)]
     t0 = time.perf_counter()
     for s, e in ev:
-        s.record(sess.stream)
+        s.record(torch.cuda.current_stream(sess.device))
         sess.render(views, variant, out=out, use_graph=True, **tuning)
-        e.record(sess.stream)
+        e.record(torch.cuda.current_stream(sess.device))
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
     per = np.array([s.elapsed_time(e) for s, e in ev])  # ms
@@ -202,8 +202,8 @@ def time_cast_kernel(sess, views, variant, steps, tuning):
     ev = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True))
           for _ in range(steps)]
     for s, e in ev:  # creates the events
-        s.record(sess.stream)
-        e.record(sess.stream)
+        s.record(torch.cuda.current_stream(sess.device))
+        e.record(torch.cuda.current_stream(sess.device))
     pairs = [(ctypes.c_void_p * 2)(s.cuda_event, e.cuda_event) for s, e in ev]
     sess.render(views, variant, out=out, use_graph=False, **tuning)
     torch.cuda.synchronize()
